@@ -11,6 +11,49 @@ namespace eigk {
 constexpr double kTiny2 = 1.0e-300;
 constexpr int kMaxSweeps = 40;
 
+// Simultaneous rotation steps (see eig.hip).
+constexpr int kMaxSteps = 12;          // per launch; then sweeps only
+constexpr int kMaxOrth = 6;            // Newton-Schulz steps of one U
+constexpr float kOrthMax = 0.25f;      // largest |U^T U - I| entry that a step starts from
+constexpr double kTangentMax = 0.5;    // tangents are clipped here
+constexpr float kColdTangent = 0.25f;  // first launch: steps only once every tangent is below
+constexpr int kOrthPeriod = 8;         // launches between Newton-Schulz steps on V
+
+// Bound on the second-order error of an entry of P: for FP32 solves below the
+// rounding of P's own entries (and that of the diagonal Z this replaces, whose
+// off-diagonals were left out up to 1e-8 sigma_i sigma_j: 5e-9), for FP64
+// solves at the rounding of the products.
+template <typename T>
+struct PTarget;
+template <>
+struct PTarget<double> {
+  static constexpr float value = 2.0e-15f;
+};
+template <>
+struct PTarget<float> {
+  static constexpr float value = 5.0e-9f;
+};
+// Entries of |U^T U - I| that need no (further) Newton-Schulz step.
+template <typename T>
+struct OrthGoal;
+template <>
+struct OrthGoal<double> {
+  static constexpr float skip = 2.0e-15f;
+};
+template <>
+struct OrthGoal<float> {
+  static constexpr float skip = 1.0e-11f;
+};
+
+// Column j of packed upper index idx = j (j + 1) / 2 + i, i <= j (idx < 2^22:
+// the float square root is exact enough to be off by at most one).
+__device__ inline int packed_col(int idx) {
+  int j = static_cast<int>((__builtin_sqrtf(8.0f * static_cast<float>(idx) + 1.0f) - 1.0f) * 0.5f);
+  if (j * (j + 1) / 2 > idx) --j;
+  else if ((j + 1) * (j + 2) / 2 <= idx) ++j;
+  return j;
+}
+
 template <typename T>
 struct RotEps;
 template <>
@@ -123,6 +166,84 @@ __device__ inline void make_rotation(double gpp, double gqq, double gpq, double&
   }
 }
 
+// What one pair (i, j) of G~ (diagonal entries di, dj, off-diagonal e) gives:
+// the first-order entry z = w[di, dj] e of the thresholded function, the two
+// factors mz, kappa of its error bound, the clipped tangent t of the rotation,
+// and whether the sweeps would rotate the pair.
+//
+// kappa is the rotation's tangent |e| / |di - dj|; for two kept values, where
+// w is smooth, |e| / min(di, dj) will do when that is smaller, and for two
+// dropped values, where w vanishes, 0.  Both hold only while the pair's values
+// stay on their side of the threshold tau^2 whatever the off-diagonals do: by
+// Gershgorin when n |e| is at most their distance from it (if that holds for
+// every pair of a row, the row's radius is within the distance).  Pairs far
+// below the threshold that are safe in this sense are not rotated at all: they
+// are the rounding noise of rank-deficient windows, and P never sees them.
+struct PairTerms {
+  double z, t;
+  float mz, kappa;
+  int rotate;
+};
+template <typename T>
+__device__ inline PairTerms pair_terms(double e, double di, double dj, double si, double sj,
+                                       double wi, double wj, double tau, int n) {
+  PairTerms o;
+  const double g = dj - di, ag = fabs(g), ae = fabs(e), tau2 = tau * tau;
+  const bool ki = si > tau, kj = sj > tau;
+  const bool safe = n * ae <= fmin(fabs(di - tau2), fabs(dj - tau2));
+  const double smax = fmax(si, sj);
+  o.rotate = off_diag_large<T>(e, di, dj) ? 1 : 0;
+  o.z = 0.0;
+  o.t = 0.0;
+  o.mz = 0.0f;
+  o.kappa = 0.0f;
+  if (ae == 0.0) return o;
+  double den = ag;  // kappa = ae / den
+  if (ki && kj) {
+    if (safe) den = fmax(ag, fmin(di, dj));
+    o.z = e * rcp_pos(si * sj) * (tau * rcp_pos(si + sj));
+    o.mz = fabsf(static_cast<float>(o.z));
+  } else if (ki || kj) {
+    o.z = e * ((ki ? wi : wj) * rcp_pos(ag));  // one above, one not: g != 0
+    o.mz = fabsf(static_cast<float>(o.z));
+  } else if (!safe) {
+    o.mz = static_cast<float>(ae * 0.5 * rcp_pos(tau2));  // the slope of w at the threshold
+  }
+  if (ki || kj || !safe) o.kappa = den > 0.0 ? static_cast<float>(ae * rcp_pos(den)) : INFINITY;
+  if (ki || kj || !safe || smax > 0.125 * tau) {
+    const double h2 = fma(g, g, 4.0 * e * e);
+    if (h2 > kTiny2) {
+      const double t = 2.0 * e * rcp_pos(ag + h2 * rsqrt_pos(h2));
+      o.t = fmin(fmax(g < 0.0 ? -t : t, -kTangentMax), kTangentMax);
+    }
+  }
+  return o;
+}
+
+// Maximum of v >= 0 over the wave (DPP within rows of 16 lanes, then the four
+// rows), added to *cell by one lane: float bits of non-negative values order
+// as integers, and a maximum does not depend on the order of its terms.  NaN
+// orders above every number.  Every lane of the wave must be active.
+template <int CTRL>
+__device__ inline unsigned dpp_max(unsigned v) {
+  const unsigned o = static_cast<unsigned>(
+      __builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false));
+  return v > o ? v : o;
+}
+__device__ inline void wave_max_to(float x, unsigned* cell) {
+  unsigned v = __float_as_uint(x);
+  v = dpp_max<0xB1>(v);   // lanes [1,0,3,2] of each quad
+  v = dpp_max<0x4E>(v);   // lanes [2,3,0,1]
+  v = dpp_max<0x141>(v);  // mirror of each half row
+  v = dpp_max<0x140>(v);  // mirror of each row
+  unsigned a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+  const unsigned c = __builtin_amdgcn_readlane(v, 32), e = __builtin_amdgcn_readlane(v, 48);
+  a = a > b ? a : b;
+  b = c > e ? c : e;
+  a = a > b ? a : b;
+  if ((threadIdx.x & 63) == 0 && a != 0u) atomicMax(cell, a);
+}
+
 // Dot product over the zero-padded length NMAX with four independent
 // partial sums (fixed trip count, so every load can be in flight at once).
 template <int NMAX, typename F>
@@ -130,22 +251,6 @@ __device__ inline double dot4(F&& term) {
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
 #pragma unroll 4
   for (int k = 0; k < NMAX; k += 4) {
-    s0 = term(k + 0, s0);
-    s1 = term(k + 1, s1);
-    s2 = term(k + 2, s2);
-    s3 = term(k + 3, s3);
-  }
-  return (s0 + s1) + (s2 + s3);
-}
-
-// The same sum over the first len terms only (len a multiple of 4, at most
-// NMAX): used where the terms past the matrix size n are exact zeros, so the
-// value is the same and the padding costs nothing.
-template <int NMAX, typename F>
-__device__ inline double dot4n(int len, F&& term) {
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#pragma unroll 2
-  for (int k = 0; k < len; k += 4) {
     s0 = term(k + 0, s0);
     s1 = term(k + 1, s1);
     s2 = term(k + 2, s2);
