@@ -57,7 +57,7 @@ struct SolveDesc {
   double* gpartials;      // groups x pstride
   void* P;                // nb x nb thresholding projector, storage precision
   double* V;              // nb x nb eigenvectors of the last eigensolve
-  double* escratch;       // class^2 doubles (112^2 or 144^2) for the wide eigensolver (else null)
+  double* escratch;       // workspace of the wide eigensolver (wide_scratch_doubles; else null)
   SolveState* st;
   int64_t* wgtrace;       // per-slot timestamps (trace builds only, else null)
   int64_t m;
@@ -116,6 +116,22 @@ struct GroupItem {
 __host__ __device__ inline constexpr int gram_blocks(int nb4) { return nb4 * (nb4 + 1) / 2; }
 __host__ __device__ inline constexpr int pstride_for(int nb) {
   return kScalars + gram_blocks((nb + 3) / 4) * 16;
+}
+
+// Workspace of the eigensolver of windows above 64 frames: class^2 doubles for
+// the Jacobi kernel, then the steps' control block and nb x nb matrices.
+constexpr int kWideSteps = 9;       // simultaneous steps of a launch at most
+constexpr int kWideMats = 10;       // G, W, S, K, T, U, C, Z and two more V
+constexpr int kWideCtlDoubles = 32;
+struct WideCtl {
+  int32_t booked;  // the iteration whose P the steps wrote last (0: none)
+  int32_t vsel;    // which of the three V buffers holds V
+};
+static_assert(sizeof(WideCtl) <= kWideCtlDoubles * sizeof(double), "control block size");
+inline int wide_class(int n) { return n <= kEigWideMaxN ? kEigWideMaxN : kEigHugeMaxN; }
+inline size_t wide_scratch_doubles(int n, int nb) {
+  const size_t c = static_cast<size_t>(wide_class(n));
+  return c * c + kWideCtlDoubles + static_cast<size_t>(kWideMats) * nb * nb;
 }
 
 }  // namespace rpca

@@ -17,6 +17,7 @@ constexpr int kMaxOrth = 6;            // Newton-Schulz steps of one U
 constexpr float kOrthMax = 0.25f;      // largest |U^T U - I| entry that a step starts from
 constexpr double kTangentMax = 0.5;    // tangents are clipped here
 constexpr float kColdTangent = 0.25f;  // first launch: steps only once every tangent is below
+constexpr float kWideFourth = 0.02f;   // wide solves: above this tangent, U to fourth order
 constexpr int kOrthPeriod = 8;         // launches between Newton-Schulz steps on V
 
 // Bound on the second-order error of an entry of P: for FP32 solves below the
@@ -243,6 +244,41 @@ __device__ inline void wave_max_to(float x, unsigned* cell) {
   a = a > b ? a : b;
   if ((threadIdx.x & 63) == 0 && a != 0u) atomicMax(cell, a);
 }
+
+// sqrt(d), or 0 for d <= 0 (the rounding of a zero eigenvalue).
+__device__ inline double sqrt_or_zero(double d) { return d > kTiny2 ? d * rsqrt_pos(d) : 0.0; }
+
+// View of a wide solve's workspace (see common.h).  cls is the class of the
+// Jacobi kernel, whose scratch comes first.
+struct WideEig {
+  WideCtl* ctl;
+  double *G, *W, *S, *K, *T, *U, *C, *Z;
+  double* V0;   // the solve's V buffer
+  double* V12;  // the two others
+  size_t q;     // nb x nb
+  __device__ explicit WideEig(const SolveDesc& d) {
+    const int c = d.n <= kEigWideMaxN ? kEigWideMaxN : kEigHugeMaxN;
+    double* p = d.escratch + static_cast<size_t>(c) * c;
+    ctl = reinterpret_cast<WideCtl*>(p);
+    p += kWideCtlDoubles;
+    q = static_cast<size_t>(d.nb) * d.nb;
+    G = p;
+    W = p + q;
+    S = p + 2 * q;
+    K = p + 3 * q;
+    T = p + 4 * q;
+    U = p + 5 * q;
+    C = p + 6 * q;
+    Z = p + 7 * q;
+    V12 = p + 8 * q;
+    V0 = d.V;
+  }
+  // V after s steps from buffer v0: the previous iteration's V stays where it
+  // is (the Jacobi kernel starts from it if the steps fail), the steps
+  // alternate between the other two buffers.
+  __device__ static int vsel(int v0, int s) { return s == 0 ? v0 : (v0 + (s & 1 ? 1 : 2)) % 3; }
+  __device__ double* v(int b) const { return b == 0 ? V0 : V12 + (b - 1) * q; }
+};
 
 // Dot product over the zero-padded length NMAX with four independent
 // partial sums (fixed trip count, so every load can be in flight at once).

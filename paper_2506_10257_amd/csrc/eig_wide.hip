@@ -28,17 +28,14 @@
 //   * a round is [apply the round's rotations] barrier [the first wave
 //     computes the next round's rotations from the updated G] barrier.
 //
-// Warm start: from the second step on, the rotations start from the previous
-// step's eigenvectors V, on G~ = V^T G V, which is nearly diagonal once the
-// iteration settles.  The two products run on the f64 matrix cores
-// (W = G V goes through a per-solve global scratch buffer, since LDS holds G
-// and V already).  For FP64 solves, and for FP32 solves that accumulate an
-// FP32 increment, V is first brought back to orthogonality by one
-// Newton-Schulz step V <- V (3I - V^T V) / 2 (also on the matrix cores); for
-// the other FP32 solves the rounding of the FP64 rotations stays far below
-// the FP32 rounding of the data and the step is skipped.  With V in global
-// memory the projector P = V diag(w) V^T is also formed on the f64 matrix
-// cores.
+// From a solve's second eigensolve on, the simultaneous steps of eig_steps.hip
+// run first; where they converge, this kernel returns at once.  Where they do
+// not, it starts from the previous iteration's eigenvectors V, brought
+// back to orthogonality by one Newton-Schulz step V <- V (3I - V^T V) / 2, on
+// G~ = V^T G V.  The products run on the f64 matrix cores (W = G V goes through
+// a per-solve global scratch buffer, since LDS holds G and V already).  With V
+// in global memory the projector P = V diag(w) V^T is also formed on the f64
+// matrix cores.
 #include <type_traits>
 
 #include "common.h"
@@ -107,6 +104,19 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   const int n = d.n;
   const int nb = d.nb;
   const int kd = st->iter;
+  const WideEig we(d);
+  if (kd == 0) {
+    // the steps' matrices are zero outside n x n, and V is in its first buffer
+    const int len = kWideMats * nb * nb;
+    for (int idx = tid; idx < len; idx += NT) we.G[idx] = 0.0;
+    if (tid == 0) {
+      we.ctl->booked = 0;
+      we.ctl->vsel = 0;
+    }
+  } else if (we.ctl->booked == kd) {
+    return;  // the steps (eig_steps.hip) wrote this iteration's P
+  }
+  double* const dV = kd == 0 ? d.V : we.v(we.ctl->vsel);
   // read now (thread 0 runs the control step), in flight during the reduction
   double pf_nXF2 = 0.0, pf_tau = 0.0;
   if (tid == 0) {
@@ -120,7 +130,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   const bool vinc = VI && warm && n <= kEigIncMaxN;
   // V rows: LDS (stride LDV) or the solve's V buffer (stride nb, nb x nb,
   // zero outside n x n)
-  const gptr<double> Vg = as_global<double>(static_cast<void*>(d.V));
+  const gptr<double> Vg = as_global<double>(static_cast<void*>(dV));
   for (int idx = tid; idx < NPK; idx += NT) Gp[idx] = 0.0;
   if constexpr (VG) {
     if (!warm) {
@@ -135,7 +145,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     for (int idx = tid; idx < NMAX * LDV; idx += NT) {
       const int i = idx / LDV, j = idx - (idx / LDV) * LDV;
       double v = (i == j && i < n) ? 1.0 : 0.0;
-      if (warm && i < n && j < n) v = d.V[i * nb + j];
+      if (warm && i < n && j < n) v = dV[i * nb + j];
       Vs[idx] = v;
     }
   }
@@ -199,10 +209,9 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     const gptr<double> Wg = as_global<double>(static_cast<void*>(d.escratch));
     // with V in global memory the products stop at nb (V is nb x nb)
     const int nt16 = VG ? nb / 16 : NT16;
-    if (std::is_same<T, double>::value || vinc) {
-      // FP64 solves, and FP32 solves that accumulate an FP32 increment: one
-      // Newton-Schulz step V <- V (3I - V^T V) / 2 first, so the rounding of
-      // the rotations does not accumulate over the solve.
+    {
+      // One Newton-Schulz step V <- V (3I - V^T V) / 2 first: the steps that
+      // V comes from leave it orthogonal to first order only (eig_steps.hip).
       // C = V^T V goes to the scratch; each wave keeps its blocks of V C in
       // registers until every wave has read V, then writes its entries of
       // the new V (each entry has one owner).
@@ -593,7 +602,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     }
     for (int idx = tid; idx < nb * nb; idx += NT) {
       const int i = idx / nb, j = idx - (idx / nb) * nb;
-      d.V[idx] = (i < n && j < n) ? Vs[i * LDV + j] : 0.0;
+      dV[idx] = (i < n && j < n) ? Vs[i * LDV + j] : 0.0;
     }
   }
   EIG_MARK(3);

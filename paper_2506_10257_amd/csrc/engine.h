@@ -68,6 +68,8 @@ struct LaneRun {
   std::vector<std::pair<int, std::pair<int, int>>> classes;  // (class key, (item offset, count))
   std::vector<std::pair<int, std::pair<int, int>>> eigs;     // (class, (id offset, count))
   int gitem_off = 0, gitem_cnt = 0;
+  int nb_max = 0;                                            // largest frame class of the lane
+  int wide_off = 0, wide_cnt = 0;                            // solves above kEigMaxN frames
   // the same for the lane's solves with a given start (extra init stage)
   std::vector<std::pair<int, std::pair<int, int>>> warm_classes, warm_eigs;
   int warm_gitem_off = 0, warm_gitem_cnt = 0;

@@ -322,8 +322,7 @@ Big big_layout(int64_t m, int64_t n, const Geo& g) {
   b.V = o; o += al256(static_cast<size_t>(g.nb) * g.nb * sizeof(double));
   b.escratch = o;
   if (n > kEigMaxN) {
-    const size_t c = static_cast<size_t>(eig_class(static_cast<int>(n)));
-    o += al256(c * c * sizeof(double));
+    o += al256(wide_scratch_doubles(static_cast<int>(n), g.nb) * sizeof(double));
   }
   b.state = o; o += al256(sizeof(SolveState));
   b.trace = o;
@@ -363,7 +362,12 @@ size_t plan_prepare(Plan& plan, const std::vector<SolveRec*>& recs, int nlanes, 
         if (eig_class(recs[i]->n) == cls) ids.push_back(i);
       const int cnt = static_cast<int>(ids.size()) - off;
       if (cnt > 0) lr.eigs.push_back({cls, {off, cnt}});
+      if (cnt > 0 && cls > kEigMaxN) {  // the wide classes' ids are contiguous
+        if (lr.wide_cnt == 0) lr.wide_off = off;
+        lr.wide_cnt += cnt;
+      }
     }
+    for (int i : lr.solves) lr.nb_max = std::max(lr.nb_max, recs[i]->geo.nb);
     lr.gitem_off = static_cast<int>(gitems.size());
     for (int i : lr.solves)
       for (int g = 0; g < recs[i]->geo.groups; ++g) gitems.push_back(GroupItem{i, g});
@@ -573,7 +577,7 @@ hipError_t enqueue_init(const Plan& plan, const Lanes& L) {
                        plan.descs, plan.items + lr.classes[c].second.first));
       ev_end(s);
     }
-    EQ(launch_reduce(lr.gitem_cnt, s, plan.descs, plan.gitems + lr.gitem_off));
+    EQ(launch_reduce(lr.gitem_cnt, reduce_chunks(lr.nb_max), s, plan.descs, plan.gitems + lr.gitem_off));
     // solves with a given start: fix mu, then the Gram of A_1 = X - S0 + Y0/mu
     for (const auto& er : lr.warm_eigs) {
       if (er.first > kEigMaxN)
@@ -587,7 +591,8 @@ hipError_t enqueue_init(const Plan& plan, const Lanes& L) {
       EQ(launch_stream(plan.dtype, wc.first, kModeWarm, wc.second.second, s, plan.descs,
                        plan.items + wc.second.first));
     if (lr.warm_gitem_cnt > 0)
-      EQ(launch_reduce(lr.warm_gitem_cnt, s, plan.descs, plan.gitems + lr.warm_gitem_off));
+      EQ(launch_reduce(lr.warm_gitem_cnt, reduce_chunks(lr.nb_max), s, plan.descs,
+                       plan.gitems + lr.warm_gitem_off));
   }
   return hipSuccess;
 }
@@ -598,14 +603,29 @@ static hipError_t enqueue_iterations_at(const Plan& plan, const Lanes& L, int it
     const LaneRun& lr = plan.lanes[l];
     hipStream_t s = L.s[l];
     for (int k = 0; k < iters; ++k) {
-      for (const auto& er : lr.eigs) {
+      // wide solves: the steps, then the sweeps where they did not converge
+      if (lr.wide_cnt > 0) {
         ev_begin(s, 1, first_iter + k, static_cast<int>(l), -1);
-        if (er.first > kEigMaxN)
-          EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s,
-                             plan.descs, plan.ids + er.second.first));
-        else
-          EQ(launch_eig(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s, plan.descs,
-                        plan.ids + er.second.first));
+        const LaunchEvents ev = t_launch_events;  // timed as one: first launch to last
+        t_launch_events = LaunchEvents{ev.start, nullptr};
+        EQ(launch_eig_steps(plan.dtype == RPCA_F32 ? 1 : 0, lr.wide_cnt, s, plan.descs,
+                            plan.ids + lr.wide_off));
+        t_launch_events = LaunchEvents{};
+        int left = lr.wide_cnt;
+        for (const auto& er : lr.eigs) {
+          if (er.first <= kEigMaxN) continue;
+          left -= er.second.second;
+          if (left == 0) t_launch_events = LaunchEvents{nullptr, ev.stop};
+          EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s, plan.descs,
+                             plan.ids + er.second.first));
+        }
+        ev_end(s);
+      }
+      for (const auto& er : lr.eigs) {
+        if (er.first > kEigMaxN) continue;
+        ev_begin(s, 1, first_iter + k, static_cast<int>(l), -1);
+        EQ(launch_eig(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s, plan.descs,
+                      plan.ids + er.second.first));
         ev_end(s);
       }
       for (size_t c = 0; c < lr.classes.size(); ++c) {
@@ -614,7 +634,7 @@ static hipError_t enqueue_iterations_at(const Plan& plan, const Lanes& L, int it
                          s, plan.descs, plan.items + lr.classes[c].second.first));
         ev_end(s);
       }
-      EQ(launch_reduce(lr.gitem_cnt, s, plan.descs, plan.gitems + lr.gitem_off));
+      EQ(launch_reduce(lr.gitem_cnt, reduce_chunks(lr.nb_max), s, plan.descs, plan.gitems + lr.gitem_off));
     }
   }
   return hipSuccess;

@@ -9,8 +9,9 @@ namespace rpca {
 
 // Kernel timing: while `start` is set, a solve-path launch on this thread
 // records its own start and end timestamps into the pair (the dispatch packet
-// carries them, so queue time between launches is not counted).  Null when
-// timing is off: then the launch is a plain one.
+// carries them, so queue time between launches is not counted).  Either may be
+// null, for a sequence of launches timed as one.  Both are null when timing is
+// off: then the launch is a plain one.
 struct LaunchEvents {
   hipEvent_t start = nullptr, stop = nullptr;
 };
@@ -18,7 +19,7 @@ extern thread_local LaunchEvents t_launch_events;
 
 #define RPCA_LAUNCH(K, G, B, SH, S, ...)                                                      \
   do {                                                                                       \
-    if (::rpca::t_launch_events.start)                                                       \
+    if (::rpca::t_launch_events.start || ::rpca::t_launch_events.stop)                       \
       hipExtLaunchKernelGGL(K, G, B, SH, S, ::rpca::t_launch_events.start,                   \
                             ::rpca::t_launch_events.stop, 0, __VA_ARGS__);                   \
     else                                                                                     \
@@ -41,7 +42,9 @@ hipError_t launch_stream_f32(int nb, int mode, bool mt, int grid, hipStream_t st
                              const SolveDesc* descs, const WorkItem* items);
 hipError_t launch_stream_f64(int nb, int mode, bool mt, int grid, hipStream_t stream,
                              const SolveDesc* descs, const WorkItem* items);
-hipError_t launch_reduce(int grid, hipStream_t stream, const SolveDesc* descs,
+// chunks: entry chunks of a group (reduce_chunks of the largest solve).
+int reduce_chunks(int nb);
+hipError_t launch_reduce(int grid, int chunks, hipStream_t stream, const SolveDesc* descs,
                          const GroupItem* items);
 hipError_t launch_gather_states(int count, hipStream_t stream, const SolveDesc* descs,
                                 SolveState* out);
@@ -56,6 +59,10 @@ int eig_class(int n);
 // (V in LDS) or kEigHugeMaxN (V in global memory).
 hipError_t launch_eig_wide(int dtype, int ncls, int grid, hipStream_t stream,
                            const SolveDesc* descs, const int32_t* ids);
+// Warm-started steps of the same solves, launched before launch_eig_wide
+// (which returns at once where they converged).
+hipError_t launch_eig_steps(int dtype, int grid, hipStream_t stream, const SolveDesc* descs,
+                            const int32_t* ids);
 // MFMA streaming kernel.  FP32 storage: nb a multiple of 16 up to 144;
 // prec 0 = FP32 rebuild / FP64 Gram, 1 = split-BF16 (3 products) for both,
 // 2 = split-BF16 (6 products).  FP64 storage: nb = 48, 64, ..., 128, both

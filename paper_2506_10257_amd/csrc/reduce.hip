@@ -1,6 +1,8 @@
 // First level of the fixed-order reduction of the streaming pass's partial
-// sums: one workgroup per (solve, group of kGroup slots) adds the group's
-// slots in slot order.  The eigensolve kernel adds the group sums in group
+// sums: one workgroup per (solve, group of kGroup slots, chunk of entries) adds
+// the group's slots in slot order.  A window of 132 frames has 9500 entries per
+// slot but, at 512 x 512 pixels, 8 groups only: with one workgroup per group
+// its pass moved 23 MB through 8 CUs.  The eigensolve kernel adds the group sums in group
 // order.  Running it as its own launch (instead of a last-arriving-workgroup
 // scheme inside the streaming kernel) keeps device-scope fences, and the L2
 // write-backs they imply, out of the streaming pass.
@@ -10,17 +12,20 @@
 namespace rpca {
 namespace {
 
+constexpr int kChunkEntries = 2 * kThreads;  // entries of a workgroup
+
 __global__ void __launch_bounds__(kThreads)
 k_reduce_groups(const SolveDesc* __restrict__ descs, const GroupItem* __restrict__ items) {
   const GroupItem gi = items[blockIdx.x];
   const SolveDesc& d = descs[gi.solve];
   if (d.st->done) return;
   const int nent = kScalars + gram_blocks((d.n + 3) >> 2) * 16;
+  const int e0 = blockIdx.y * kChunkEntries, e1 = min(nent, e0 + kChunkEntries);
   const int lo = gi.group * kGroup;
   const int cnt = min(kGroup, d.slots - lo);
   const double* src = d.partials + static_cast<size_t>(lo) * d.pstride;
   double* dst = d.gpartials + static_cast<size_t>(gi.group) * d.pstride;
-  for (int idx = threadIdx.x; idx < nent; idx += kThreads) {
+  for (int idx = e0 + threadIdx.x; idx < e1; idx += kThreads) {
     double v[kGroup];
 #pragma unroll
     for (int q = 0; q < kGroup; ++q)
@@ -66,10 +71,14 @@ hipError_t launch_reset_states(int count, hipStream_t stream, const SolveDesc* d
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(int grid, hipStream_t stream, const SolveDesc* descs,
+int reduce_chunks(int nb) {
+  return (kScalars + gram_blocks((nb + 3) >> 2) * 16 + kChunkEntries - 1) / kChunkEntries;
+}
+
+hipError_t launch_reduce(int grid, int chunks, hipStream_t stream, const SolveDesc* descs,
                          const GroupItem* items) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce_groups, dim3(grid), dim3(kThreads), 0, stream, descs, items);
+  hipLaunchKernelGGL(k_reduce_groups, dim3(grid, chunks), dim3(kThreads), 0, stream, descs, items);
   return hipGetLastError();
 }
 
