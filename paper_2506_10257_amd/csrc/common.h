@@ -121,7 +121,7 @@ __host__ __device__ inline constexpr int pstride_for(int nb) {
 // Workspace of the eigensolver of windows above 64 frames: class^2 doubles for
 // the Jacobi kernel, then the steps' control block and nb x nb matrices.
 constexpr int kWideSteps = 9;       // simultaneous steps of a launch at most
-constexpr int kWideMats = 10;       // G, W, S, K, T, U, C, Z and two more V
+constexpr int kWideMats = 12;       // G, W, S, K, T, U, C, Z, two more V, two V^T
 constexpr int kWideCtlDoubles = 32;
 struct WideCtl {
   int32_t booked;  // the iteration whose P the steps wrote last (0: none)

@@ -253,6 +253,7 @@ __device__ inline double sqrt_or_zero(double d) { return d > kTiny2 ? d * rsqrt_
 struct WideEig {
   WideCtl* ctl;
   double *G, *W, *S, *K, *T, *U, *C, *Z;
+  double* VT[2];  // V^T of the even and of the odd steps
   double* V0;   // the solve's V buffer
   double* V12;  // the two others
   size_t q;     // nb x nb
@@ -271,6 +272,8 @@ struct WideEig {
     C = p + 6 * q;
     Z = p + 7 * q;
     V12 = p + 8 * q;
+    VT[0] = p + 10 * q;
+    VT[1] = p + 11 * q;
     V0 = d.V;
   }
   // V after s steps from buffer v0: the previous iteration's V stays where it

@@ -6,7 +6,7 @@
 // P = V Z V^T with Z the first-order expansion of the thresholding function at
 // the diagonal of G~.  Here the matrices (up to 166 KB each) stay in the
 // solve's workspace, that is in the L2, and every product runs on the f64
-// matrix cores, two 16 x 16 blocks of a row of blocks per wave at a time:
+// matrix cores, 2 x 2 blocks of 16 x 16 per wave at a time:
 //
 //   reduce   G = sum of the group partials, control step (stopping test)
 //   W = G V;  S = V^T W, C = V^T V
@@ -37,81 +37,137 @@ using namespace eigk;
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-constexpr int kStepThreads = 1024;
+constexpr int kStepThreads = 512;
 constexpr int kStepWaves = kStepThreads / 64;
 
-// Blocks (bi, bj) and (bi, bj + 1) of X^T Y (TA: of X Y; TB: of X^T Y^T), the
-// second one only when `two`.  A operand lane l = entry (l % 16, l / 16) of the
-// left factor, B operand lane l = entry (l / 16, l % 16) of the right one;
-// result lane l, register r = entry (l / 16 + 4r, l % 16).
-template <bool TA, bool TB>
-__device__ inline void blocks2(const double* Xp, const double* Yp, int nb, int bi, int bj, bool two,
-                               d4& s0, d4& s1) {
-  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
-  const int bj1 = two ? bj + 1 : bj;
-  gptr<const double> x = as_global<double>(
-      static_cast<const void*>(TA ? Xp + (16 * bi + lc) * nb + lr : Xp + lr * nb + 16 * bi + lc));
-  gptr<const double> y0 = as_global<double>(
-      static_cast<const void*>(TB ? Yp + (16 * bj + lc) * nb + lr : Yp + lr * nb + 16 * bj + lc));
-  gptr<const double> y1 = as_global<double>(
-      static_cast<const void*>(TB ? Yp + (16 * bj1 + lc) * nb + lr : Yp + lr * nb + 16 * bj1 + lc));
-  const int dx = TA ? 4 : 4 * nb, dy = TB ? 4 : 4 * nb;
-  s0 = d4{0.0, 0.0, 0.0, 0.0};
-  s1 = d4{0.0, 0.0, 0.0, 0.0};
+// The 2 x 2 blocks (bi + p, bj + q) of X^T Y into s[p][q]; blocks past the last
+// row or column (or, SYM, below the diagonal) are skipped.  A operand lane l =
+// X entry (l / 16, l % 16), B operand lane l = Y entry (l / 16, l % 16) of a
+// step's four rows; result lane l, register r = entry (l / 16 + 4r, l % 16).
+// Both operands read 128 contiguous bytes per row, and four loads of 512 B feed
+// four products of 64 cycles.
+template <bool SYM>
+__device__ inline void blocks4(const double* Xp, const double* Yp, int nb, int bi, int bj, d4 (&s)[2][2]) {
+  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15, last = (nb >> 4) - 1;
+  gptr<const double> x[2], y[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    x[p] = as_global<double>(static_cast<const void*>(Xp + lr * nb + 16 * min(bi + p, last) + lc));
+    y[p] = as_global<double>(static_cast<const void*>(Yp + lr * nb + 16 * min(bj + p, last) + lc));
+#pragma unroll
+    for (int q = 0; q < 2; ++q) s[p][q] = d4{0.0, 0.0, 0.0, 0.0};
+  }
+  const bool row1 = bi < last && !(SYM && bi + 1 > bj + 1), col1 = bj < last;
+  const bool both = row1 && col1, low = row1 && !(SYM && bi + 1 > bj);
+  const int dk = 4 * nb;
 #pragma unroll 1
   for (int k0 = 0; k0 < nb; k0 += 16) {
-    double a[4], b[4], c[4];
+    double a[2][4], b[2][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      a[k] = x[k * dx];
-      b[k] = y0[k * dy];
-      c[k] = y1[k * dy];
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        a[p][k] = x[p][k * dk];
+        b[p][k] = y[p][k * dk];
+      }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      x[p] += 4 * dk;
+      y[p] += 4 * dk;
     }
-    x += 4 * dx;
-    y0 += 4 * dy;
-    y1 += 4 * dy;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k], b[k], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k], c[k], s1, 0, 0, 0);
+    for (int k = 0; k < 4; ++k) s[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][k], b[0][k], s[0][0], 0, 0, 0);
+    if (col1) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0][k], b[1][k], s[0][1], 0, 0, 0);
+    }
+    if (low) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][k], b[0][k], s[1][0], 0, 0, 0);
+    }
+    if (both) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1][k], b[1][k], s[1][1], 0, 0, 0);
     }
   }
 }
 
-// Every block of a product (SYM: the upper ones), as pairs of blocks of one
-// block row, units u, u + kStepWaves, ... of this wave.  `u` is advanced past
-// the product's units, so that two products with no barrier between them share
-// the waves evenly.  out(i, j, value) is called for each entry (SYM: i <= j).
-template <bool SYM, bool TA = false, bool TB = false, typename Out>
+// Every block of X^T Y (SYM: the upper ones), in units of 2 x 2 blocks: the
+// units u, u + kStepWaves, ... of this wave.  `u` is advanced past the product's
+// units, so that two products with no barrier between them share the waves
+// evenly.  out(bi, bj, block) is called for each 16 x 16 block.
+template <bool SYM, typename Out>
 __device__ inline void product(int& u, const double* X, const double* Y, int nb, Out&& out) {
-  const int nt = nb >> 4, l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
-  int units = 0;
-  for (int b = 0; b < nt; ++b) units += ((SYM ? nt - b : nt) + 1) >> 1;
+  const int nt = nb >> 4, n2 = (nt + 1) >> 1;
+  const int units = SYM ? n2 * (n2 + 1) / 2 : n2 * n2;
   for (; u < units; u += kStepWaves) {
-    int bi = 0, v = u;
-    for (;; ++bi) {
-      const int row = ((SYM ? nt - bi : nt) + 1) >> 1;
-      if (v < row) break;
-      v -= row;
-    }
-    const int bj = (SYM ? bi : 0) + 2 * v;
-    const bool two = bj + 1 < nt;
-    d4 s0, s1;
-    blocks2<TA, TB>(X, Y, nb, bi, bj, two, s0, s1);
+    const int uj = SYM ? packed_col(u) : u % n2, ui = SYM ? u - uj * (uj + 1) / 2 : u / n2;
+    const int bi = 2 * ui, bj = 2 * uj;
+    d4 s[2][2];
+    blocks4<SYM>(X, Y, nb, bi, bj, s);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = 16 * bi + lr + 4 * r, j = 16 * bj + lc;
-      if (!SYM || i <= j) out(i, j, s0[r]);
-      if (two) out(i, j + 16, s1[r]);
-    }
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (bi + p < nt && bj + q < nt && !(SYM && bi + p > bj + q)) out(bi + p, bj + q, s[p][q]);
   }
   u -= units;
+}
+
+// One lane's entries of a 16 x 16 block and their transposes, through the
+// wave's own LDS buffer (16 rows of 17): a transposed block is then stored in
+// rows of 128 bytes too, instead of 64 scattered entries per store.
+constexpr int kTrLd = 17;
+__device__ inline d4 transposed(const d4& v, double* tb) {
+  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
+  d4 t;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) tb[(lr + 4 * r) * kTrLd + lc] = v[r];
+  __builtin_amdgcn_wave_barrier();  // LDS operations of a wave complete in order
+#pragma unroll
+  for (int r = 0; r < 4; ++r) t[r] = tb[lc * kTrLd + lr + 4 * r];
+  __builtin_amdgcn_wave_barrier();
+  return t;
+}
+template <typename T>
+__device__ inline void store_block(T* M, int nb, int bi, int bj, const d4& v) {
+  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
+  const gptr<T> p = as_global<T>(static_cast<void*>(M + (16 * bi + lr) * nb + 16 * bj + lc));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) p[4 * r * nb] = static_cast<T>(v[r]);
+}
+// Upper block (bi, bj) of a symmetric matrix h + k with h symmetric and k
+// antisymmetric (entries of h, k; k may be zero), and its mirror image h - k.
+// On the diagonal the entries above it decide both.
+template <typename T>
+__device__ inline void store_mirrored(T* M, int nb, int bi, int bj, const d4& h, const d4& k, double* tb) {
+  const d4 lo = transposed(h - k, tb);
+  if (bi != bj) {
+    store_block(M, nb, bi, bj, h + k);
+    store_block(M, nb, bj, bi, lo);
+  } else {
+    const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
+    d4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = lr + 4 * r <= lc ? h[r] + k[r] : lo[r];
+    store_block(M, nb, bi, bj, v);
+  }
+}
+__device__ inline d4 load_block(const double* M, int nb, int bi, int bj) {
+  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
+  const gptr<const double> p =
+      as_global<double>(static_cast<const void*>(M + (16 * bi + lr) * nb + 16 * bj + lc));
+  d4 v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = p[4 * r * nb];
+  return v;
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kStepThreads)
 k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
   __shared__ double dg[kEigHugeMaxN], sg[kEigHugeMaxN], w[kEigHugeMaxN], sd[kEigHugeMaxN];
+  __shared__ double tbuf[kStepWaves][16 * kTrLd];
   __shared__ double scal[kScalars];
   __shared__ unsigned mx[2][4];
   __shared__ int s_go;
@@ -121,6 +177,21 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   SolveState* st = d.st;
   // a solve's first eigensolve is the Jacobi kernel's
   if (st->done || st->iter == 0) return;
+#ifdef RPCA_TRACE
+  int64_t tprev = RPCA_NOW();
+#define STEP_MARK(i)                              \
+  do {                                            \
+    if (tid == 0) {                               \
+      const int64_t tnow_ = RPCA_NOW();           \
+      st->trace[i] += tnow_ - tprev;              \
+      tprev = tnow_;                              \
+    }                                             \
+  } while (0)
+#else
+#define STEP_MARK(i) \
+  do {               \
+  } while (0)
+#endif
   const WideEig e(d);
   const int n = d.n, nb = d.nb, kd = st->iter;
   double pf_nXF2 = 0.0, pf_tau = 0.0;
@@ -168,27 +239,34 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   }
   __syncthreads();
   if (!s_go) return;
+  STEP_MARK(0);
   const double tau = s_tau;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  auto put = [&](double* M) { return [M, nb](int i, int j, double v) { M[i * nb + j] = v; }; };
+  const int l = tid & 63, lr = l >> 4, lc = l & 15, nt = nb >> 4;
+  double* tb = tbuf[wv];
+  const d4 zero = {0.0, 0.0, 0.0, 0.0};
+  auto put = [&](double* M) { return [M, nb](int bi, int bj, const d4& v) { store_block(M, nb, bi, bj, v); }; };
   auto put_sym = [&](double* M) {
-    return [M, nb](int i, int j, double v) {
-      M[i * nb + j] = v;
-      M[j * nb + i] = v;
-    };
+    return [=](int bi, int bj, const d4& v) { store_mirrored(M, nb, bi, bj, v, zero, tb); };
   };
 
-  // W = G V (G symmetric), S = V^T W, C = V^T V
+  // W = G V (G symmetric), S = V^T W, C = V^T V (C: upper blocks only)
   const int v0 = e.ctl->vsel;
-  double* V = e.v(v0);
+  const double* V = e.v(v0);
   int u = wv;
   product<false>(u, e.G, V, nb, put(e.W));
   __syncthreads();
   u = wv;
   product<true>(u, V, e.W, nb, put_sym(e.S));
-  product<true>(u, V, V, nb, put_sym(e.C));
+  product<true>(u, V, V, nb, put(e.C));
+  // V^T, for the products with V as the left factor (or V^T as the right one)
+  for (int t = wv; t < nt * nt; t += kStepWaves) {
+    const int bi = t / nt, bj = t - bi * nt;
+    store_block(e.VT[0], nb, bj, bi, transposed(load_block(V, nb, bi, bj), tb));
+  }
   __syncthreads();
 
+  STEP_MARK(2);
   int s = 0;
   bool ok = false;
   for (;; ++s) {
@@ -201,30 +279,35 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       dg[tid] = di;
       sg[tid] = si;
       w[tid] = wi;
-      e.Z[tid * nb + tid] = fma(-m, wi, wi);
-      e.K[tid * nb + tid] = 0.0;
     }
     __syncthreads();
     float mz = 0.0f, mk = 0.0f, mm = 0.0f, mt = 0.0f;
-    for (int idx = tid; idx < n * (n + 1) / 2; idx += kStepThreads) {
-      const int j = packed_col(idx), i = idx - j * (j + 1) / 2;
-      const double c = e.C[i * nb + j];
-      if (i == j) {
-        mm = fmaxf(mm, fabsf(static_cast<float>(c - 1.0)));
-        if (!(c == c)) mm = INFINITY;
-        continue;
+    for (int t = wv; t < nt * (nt + 1) / 2; t += kStepWaves) {
+      const int bj = packed_col(t), bi = t - bj * (bj + 1) / 2;
+      const d4 cb = load_block(e.C, nb, bi, bj), sb = load_block(e.S, nb, bi, bj);
+      const int j = 16 * bj + lc;
+      d4 z = zero, k = zero;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * bi + lr + 4 * r;
+        if (i > j || j >= n) continue;
+        if (i == j) {
+          const double m = cb[r] - 1.0;
+          z[r] = fma(-m, w[i], w[i]);
+          mm = fmaxf(mm, cb[r] == cb[r] ? fabsf(static_cast<float>(m)) : INFINITY);
+        } else {
+          const double el = fma(-0.5 * cb[r], sd[i] + sd[j], sb[r]);
+          const PairTerms pt = pair_terms<T>(el, dg[i], dg[j], sg[i], sg[j], w[i], w[j], tau, n);
+          z[r] = fma(-0.5 * cb[r], w[i] + w[j], pt.z);
+          k[r] = pt.t;
+          mz = fmaxf(mz, pt.mz);
+          mk = fmaxf(mk, pt.kappa);
+          mt = fmaxf(mt, fabsf(static_cast<float>(pt.t)));
+          mm = fmaxf(mm, fabsf(static_cast<float>(cb[r])));
+        }
       }
-      const double el = fma(-0.5 * c, sd[i] + sd[j], e.S[i * nb + j]);
-      const PairTerms pt = pair_terms<T>(el, dg[i], dg[j], sg[i], sg[j], w[i], w[j], tau, n);
-      const double z = fma(-0.5 * c, w[i] + w[j], pt.z);
-      e.Z[i * nb + j] = z;
-      e.Z[j * nb + i] = z;
-      e.K[i * nb + j] = pt.t;
-      e.K[j * nb + i] = -pt.t;
-      mz = fmaxf(mz, pt.mz);
-      mk = fmaxf(mk, pt.kappa);
-      mt = fmaxf(mt, fabsf(static_cast<float>(pt.t)));
-      mm = fmaxf(mm, fabsf(static_cast<float>(c)));
+      store_mirrored(e.Z, nb, bi, bj, z, zero, tb);
+      store_mirrored(e.K, nb, bi, bj, zero, k, tb);
     }
     wave_max_to(mz, &mp[0]);
     wave_max_to(mk, &mp[1]);
@@ -236,64 +319,68 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     mm = __uint_as_float(mp[2]);
     mt = __uint_as_float(mp[3]);
     if (tid < 4) mx[(s + 1) & 1][tid] = 0u;  // last read before the barrier above
+    STEP_MARK(1);
     if (!(mm < kOrthMax)) break;
     ok = static_cast<float>(n) * fmaxf(mz, mm) * fmaxf(mk, mm) < PTarget<T>::value;
     if (ok || s == kWideSteps) break;
 
     // U = I + K + T/2 - M/2, T = K^2 = -K^T K (to fourth order for large K)
-    const bool fourth = mt > kWideFourth;
+    auto eye = [&](int bi, int bj) {  // I - M/2
+      d4 h = zero;
+      const d4 c = load_block(e.C, nb, bi, bj);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double id = bi == bj && lr + 4 * r == lc ? 1.0 : 0.0;
+        h[r] = 16 * bj + lc < n ? fma(-0.5, c[r] - id, id) : id;
+      }
+      return h;
+    };
     u = wv;
-    if (!fourth) {
-      product<true>(u, e.K, e.K, nb, [&](int i, int j, double v) {
-        const double id = i == j ? 1.0 : 0.0, k = e.K[i * nb + j];
-        const double m = j < n ? e.C[i * nb + j] - id : 0.0;
-        const double h = id - 0.5 * (v + m);
-        e.U[i * nb + j] = h + k;
-        if (i != j) e.U[j * nb + i] = h - k;
+    if (!(mt > kWideFourth)) {
+      product<true>(u, e.K, e.K, nb, [&](int bi, int bj, const d4& v) {
+        store_mirrored(e.U, nb, bi, bj, eye(bi, bj) - 0.5 * v, load_block(e.K, nb, bi, bj), tb);
       });
     } else {
-      product<true>(u, e.K, e.K, nb, [&](int i, int j, double v) {
-        e.T[i * nb + j] = -v;
-        e.T[j * nb + i] = -v;
-      });
+      product<true>(u, e.K, e.K, nb,
+                    [&](int bi, int bj, const d4& v) { store_mirrored(e.T, nb, bi, bj, -v, zero, tb); });
       __syncthreads();
-      // (K T into W, T^2 straight into U; an entry of both has one owner)
+      // K T = -K^T T into W, then T^2 and U (a block of both has one owner)
       u = wv;
-      product<true>(u, e.K, e.T, nb, [&](int i, int j, double v) { e.W[i * nb + j] = -v; });
+      product<true>(u, e.K, e.T, nb, [&](int bi, int bj, const d4& v) { store_block(e.W, nb, bi, bj, -v); });
       u = wv;
-      product<true>(u, e.T, e.T, nb, [&](int i, int j, double v) {
-        const double id = i == j ? 1.0 : 0.0;
-        const double m = j < n ? e.C[i * nb + j] - id : 0.0;
-        const double h = id + 0.5 * (e.T[i * nb + j] - m) + v * (1.0 / 24.0);
-        const double a = i == j ? 0.0 : fma(e.W[i * nb + j], 1.0 / 6.0, e.K[i * nb + j]);
-        e.U[i * nb + j] = h + a;
-        if (i != j) e.U[j * nb + i] = h - a;
+      product<true>(u, e.T, e.T, nb, [&](int bi, int bj, const d4& v) {
+        const d4 h = eye(bi, bj) + 0.5 * load_block(e.T, nb, bi, bj) + v * (1.0 / 24.0);
+        const d4 k = load_block(e.K, nb, bi, bj) + load_block(e.W, nb, bi, bj) * (1.0 / 6.0);
+        store_mirrored(e.U, nb, bi, bj, h, k, tb);
       });
     }
     __syncthreads();
-    // W = S U, V' = V U;  S = U^T W, C = V'^T V'
+    // W = S U, V' = V U (and its transpose);  S = U^T W, C = V'^T V'
     double* Vn = e.v(WideEig::vsel(v0, s + 1));
     u = wv;
     product<false>(u, e.S, e.U, nb, put(e.W));
-      product<false, true>(u, V, e.U, nb, put(Vn));
+    product<false>(u, e.VT[s & 1], e.U, nb, [&](int bi, int bj, const d4& v) {
+      store_block(Vn, nb, bi, bj, v);
+      store_block(e.VT[~s & 1], nb, bj, bi, transposed(v, tb));
+    });
     V = Vn;
     __syncthreads();
     u = wv;
     product<true>(u, e.U, e.W, nb, put_sym(e.S));
-      product<true>(u, V, V, nb, put_sym(e.C));
+    product<true>(u, V, V, nb, put(e.C));
     __syncthreads();
+    STEP_MARK(2);
   }
   if (!ok) return;  // the Jacobi kernel takes over, from V at v0
 
   // P = V (Z V^T) (exactly symmetric)
+  const double* Vt = e.VT[s & 1];
   u = wv;
-  product<false, false, true>(u, e.Z, V, nb, put(e.W));
+  product<false>(u, e.Z, Vt, nb, put(e.W));
   __syncthreads();
-  const gptr<T> P = as_global<T>(d.P);
   u = wv;
-  product<true, true>(u, V, e.W, nb, [&](int i, int j, double v) {
-    P[i * nb + j] = static_cast<T>(v);
-    P[j * nb + i] = static_cast<T>(v);
+  product<true>(u, Vt, e.W, nb, [&](int bi, int bj, const d4& v) {
+    store_mirrored(static_cast<T*>(d.P), nb, bi, bj, v, zero, tb);
   });
   const int rank = __syncthreads_count(tid < n && w[tid] != 0.0);
   if (tid == 0) {
@@ -301,8 +388,13 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     e.ctl->booked = kd + 1;
     st->rank = rank;
     st->sweeps = 0;
+#ifdef RPCA_TRACE
+    st->sweeps_total += s;
+#endif
     st->iter = kd + 1;
   }
+  STEP_MARK(3);
+#undef STEP_MARK
 }
 
 }  // namespace
