@@ -802,6 +802,124 @@ int lease_lanes(int dev, int nlanes, int count, LaneLease& lease, Lanes& view) {
   return RPCA_OK;
 }
 
+// Whole-solve kernel (resident_impl.h): chosen for a single solve on the
+// register kernel with one tile per slot whose tiles fit the device's CUs, two
+// per workgroup, or four for FP32 windows of up to 20 frames.  Measured at 512 x
+// 512 x 20 (FP32) and 128 x 128 x 20 (FP64): see resident_impl.h.
+constexpr int kResidentMaxIt = 20000;  // bounds one launch (about half a second)
+constexpr int kNotRun = INT32_MIN;     // run_resident: take the launched path
+std::mutex g_resident_mu[64];          // one such solve at a time per device
+
+struct ResidentPlan {
+  int nb = 0, threads = 0, grid = 0, tpw = 0, ushift = 0;
+};
+
+bool resident_plan(const SolveRec& r, int dtype, int cus, ResidentPlan& p) {
+  if (r.geo.kind != 0 || r.geo.tps != 1 || r.maxit > kResidentMaxIt) return false;
+  const bool f32 = dtype == RPCA_F32;
+  p.nb = r.n <= 10 ? 10 : (r.n <= 16 ? 16 : (r.n <= 20 ? 20 : 32));
+  if (r.n > (f32 ? 32 : 20)) return false;
+  p.grid = 0;
+  for (int tpw : {1, 2, 4}) {
+    if (tpw == 4 && (!f32 || p.nb > 20)) break;
+    const int grid = (r.geo.tiles + tpw - 1) / tpw;
+    if (grid <= cus && grid <= 256) {
+      p.tpw = tpw;
+      p.grid = grid;
+      break;
+    }
+  }
+  if (p.grid == 0) return false;
+  p.threads = p.tpw == 4 ? 1024 : 512;
+  p.ushift = 0;
+  while ((1 << p.ushift) < p.grid) ++p.ushift;
+  return true;
+}
+
+int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hipStream_t user) {
+  static std::atomic<int> cus[64];
+  if (dev < 0 || dev >= 64) return kNotRun;
+  int ncu = cus[dev].load(std::memory_order_relaxed);
+  if (ncu == 0) {
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return kNotRun;
+    }
+    cus[dev].store(ncu, std::memory_order_relaxed);
+  }
+  ResidentPlan rp;
+  if (!resident_plan(rec, dtype, ncu, rp)) return kNotRun;
+  // A second such grid would wait for CUs that the first one holds.
+  std::unique_lock<std::mutex> lk(g_resident_mu[dev], std::try_to_lock);
+  if (!lk.owns_lock()) return kNotRun;
+
+  LaneLease lease;
+  Lanes L;
+  int rc = lease_lanes(dev, 1, 2, lease, L);
+  if (rc != RPCA_OK) return rc;
+  hipStream_t s = L.s[0];
+  hipError_t e = hipStreamSynchronize(user);  // inputs are produced on the caller's stream
+  if (e != hipSuccess) {
+    set_error("hipStreamSynchronize(caller stream)", e);
+    return RPCA_ERR_DEVICE;
+  }
+  // state and the lost flag first (read back together), then the words
+  const size_t head = al256(sizeof(SolveState) + sizeof(uint64_t));
+  const size_t nent = static_cast<size_t>(pstride_for(rec.n));
+  const size_t parts = al256(nent * rp.grid * 2 * sizeof(uint64_t)), sums = al256(nent * 2 * sizeof(uint64_t));
+  char* mem = nullptr;
+  e = hipMallocAsync(reinterpret_cast<void**>(&mem), head + parts + sums, s);
+  if (e != hipSuccess || mem == nullptr) {
+    set_error("hipMallocAsync(exchange)", e);
+    (void)hipGetLastError();
+    return RPCA_ERR_NOMEM;
+  }
+  Plan plan;  // the descriptor, without workspace
+  SolveRec r = rec;
+  r.mem = nullptr;
+  std::vector<SolveRec*> one{&r};
+  r.lane = 0;
+  (void)plan_prepare(plan, one, 1, dtype);
+  SolveDesc d;
+  std::memcpy(&d, plan.host.data(), sizeof(d));
+  d.st = reinterpret_cast<SolveState*>(mem);
+  ResidentBuf rb{};
+  rb.lost = reinterpret_cast<uint32_t*>(mem + sizeof(SolveState));
+  rb.parts = reinterpret_cast<uint64_t*>(mem + head);
+  rb.sums = reinterpret_cast<uint64_t*>(mem + head + parts);
+  rb.tpw = rp.tpw;
+  rb.ushift = rp.ushift;
+  e = launch_zero(reinterpret_cast<uint64_t*>(mem), (head + parts + sums) / sizeof(uint64_t), s);
+  if (e == hipSuccess)
+    e = dtype == RPCA_F32 ? launch_resident_f32(rp.nb, rp.threads, rp.grid, s, d, rb)
+                          : launch_resident_f64(rp.nb, rp.threads, rp.grid, s, d, rb);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(L.pinned[0], mem, sizeof(SolveState) + sizeof(uint64_t), hipMemcpyDeviceToHost, s);
+  const hipError_t ef = hipFreeAsync(mem, s);
+  if (e == hipSuccess) e = ef;
+  const hipError_t es = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = es;
+  if (e != hipSuccess) {
+    set_error("whole-solve kernel", e);
+    (void)hipGetLastError();
+    return RPCA_ERR_DEVICE;
+  }
+  SolveState st;
+  uint32_t lost = 0;
+  std::memcpy(&st, L.pinned[0], sizeof(st));
+  std::memcpy(&lost, reinterpret_cast<const char*>(L.pinned[0]) + sizeof(st), sizeof(lost));
+#ifdef RPCA_TRACE
+  std::fprintf(stderr, "[resident] us/iter: eig %.2f update %.2f gram %.2f partial %.2f hop1+sum %.2f hop2 %.2f (lost %u)\n",
+               st.trace[0] * 0.01 / st.iter, st.trace[1] * 0.01 / st.iter, st.trace[2] * 0.01 / st.iter,
+               st.trace[3] * 0.01 / st.iter, st.trace[4] * 0.01 / st.iter, st.trace[5] * 0.01 / st.iter, lost);
+#endif
+  if (lost != 0) return kNotRun;  // a wait ran out of time: nothing was kept
+  prob.iterations = st.iter;
+  prob.status = st.status;
+  prob.residual = st.resid;
+  return st.status;
+}
+
 int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream_t user) {
   g_last_error[0] = '\0';
   if (count < 1 || probs == nullptr) return RPCA_ERR_ARG;
@@ -832,6 +950,11 @@ int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStrea
     }
   }
   setup_pool(dev);
+
+  if (count == 1 && !prof) {
+    const int rrc = run_resident(probs[0], recs[0], dtype, dev, user);
+    if (rrc != kNotRun) return rrc;
+  }
 
   const bool use_graph = !prof && !graphs_disabled();
   int rc = RPCA_OK;

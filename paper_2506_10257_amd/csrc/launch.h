@@ -77,4 +77,19 @@ bool set_eig_threads(int dtype, int ncls, int nt);
 hipError_t launch_eig(int dtype, int ncls, int grid, hipStream_t stream, const SolveDesc* descs,
                       const int32_t* ids);
 
+// Whole-solve kernel (resident_impl.h): its exchange buffers.
+struct ResidentBuf {
+  uint64_t* parts;  // 2 words per (entry, workgroup)
+  uint64_t* sums;   // 2 words per entry
+  uint32_t* lost;   // set when a wait ran out of time
+  int32_t tpw;      // 256-row tiles per workgroup (1, 2 or 4)
+  int32_t ushift;   // log2 of the workgroup count, rounded up
+};
+hipError_t launch_resident_f32(int nb, int threads, int grid, hipStream_t stream, const SolveDesc& d,
+                               const ResidentBuf& rb);
+hipError_t launch_resident_f64(int nb, int threads, int grid, hipStream_t stream, const SolveDesc& d,
+                               const ResidentBuf& rb);
+// Zero `words` 8-byte words.
+hipError_t launch_zero(uint64_t* p, size_t words, hipStream_t stream);
+
 }  // namespace rpca

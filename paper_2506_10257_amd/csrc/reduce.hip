@@ -12,6 +12,9 @@
 namespace rpca {
 namespace {
 
+// A group's slots are added in quads, (v0 + v1) + (v2 + v3), and the quads in
+// order: a workgroup of the whole-solve kernel (resident_impl.h) that holds four
+// tiles can then hand on one sum.
 constexpr int kChunkEntries = 2 * kThreads;  // entries of a workgroup
 
 __global__ void __launch_bounds__(kThreads)
@@ -30,10 +33,10 @@ k_reduce_groups(const SolveDesc* __restrict__ descs, const GroupItem* __restrict
 #pragma unroll
     for (int q = 0; q < kGroup; ++q)
       v[q] = q < cnt ? src[static_cast<size_t>(q) * d.pstride + idx] : 0.0;
-    double sum = v[0];
+    double sum = (v[0] + v[1]) + (v[2] + v[3]);
 #pragma unroll
-    for (int q = 1; q < kGroup; ++q)
-      if (q < cnt) sum += v[q];
+    for (int q = 4; q < kGroup; q += 4)
+      if (q < cnt) sum += (v[q] + v[q + 1]) + (v[q + 2] + v[q + 3]);
     dst[idx] = sum;
   }
 }
@@ -56,7 +59,20 @@ k_reset_states(const SolveDesc* __restrict__ descs, int count) {
   }
 }
 
+__global__ void __launch_bounds__(kThreads)
+k_zero(uint64_t* __restrict__ p, size_t words) {
+  const size_t stride = static_cast<size_t>(gridDim.x) * kThreads;
+  for (size_t i = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x; i < words; i += stride) p[i] = 0;
+}
+
 }  // namespace
+
+hipError_t launch_zero(uint64_t* p, size_t words, hipStream_t stream) {
+  const size_t g = (words + kThreads - 1) / kThreads;
+  hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>(g < 1024 ? g : 1024)), dim3(kThreads), 0, stream, p,
+                     words);
+  return hipGetLastError();
+}
 
 hipError_t launch_gather_states(int count, hipStream_t stream, const SolveDesc* descs,
                                 SolveState* out) {

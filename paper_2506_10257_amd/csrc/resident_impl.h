@@ -1,0 +1,464 @@
+// One whole solve in one launch, its rows in registers.
+//
+// A window of up to 32 frames whose X, S and Y fit the register files of the
+// chip (134 MB; 512 x 512 x 20 in FP32 takes 63 MB) needs no memory traffic
+// between iterations but the reduction of its Gram partials.  Each workgroup
+// (one per CU at most) keeps up to four 256-row tiles, one thread per row, and
+// runs every iteration: eigensolve, update of its rows, Gram partial, all-to-all
+// sum.  The eigensolve runs in every workgroup, on the same sums, so its
+// projector needs no broadcast and V never leaves the LDS.  At 512 x 512 x 20
+// an iteration of the launched path (eigensolve, update, reduction) is bound by
+// the update's 105 MB (27 us), three launches and the eigensolve in series; here
+// the update is the arithmetic of 1024 rows per CU.
+//
+// Sum across workgroups: two hops through memory, no fences.  Every 8-byte word
+// carries 32 bits of a double and the sequence number of the exchange, is
+// written by one relaxed agent-scope store (which goes through to memory) and
+// polled by relaxed agent-scope loads, so a word is valid as soon as its number
+// is right and nothing else has to be ordered:
+//   1. workgroup w writes each entry of its partial (Gram blocks, residual);
+//   2. workgroup e adds entry e (and e + grid, ...) over all workgroups, in the
+//      order of k_reduce_groups and k_eig, and writes the sum;
+//   3. every workgroup reads all sums.
+// One buffer per hop is enough: a workgroup writes its next partial only after
+// it has every sum, that is after every partial of this exchange was read, and
+// writes a next sum only after every partial of the next exchange is there,
+// that is after every workgroup has read the sums of this one.
+//
+// Every wait ends: the grid has at most one workgroup per CU, but nothing
+// guarantees that all of them run at once (another process, other streams), so
+// a wait is bounded by the wall clock.  A workgroup that gives up leaves the
+// kernel; the others then give up as well, and the caller runs the launched
+// path from the unchanged inputs.
+//
+// The arithmetic is that of k_stream, k_reduce_groups and k_eig operation for
+// operation, so the results are bitwise those of the launched path.
+#pragma once
+
+#include "common.h"
+#include "eig_core.h"
+#include "launch.h"
+#include "stream_impl.h"
+
+namespace rpca {
+namespace {
+
+// Wall clock ticks (100 MHz): first exchange (workgroups still being placed),
+// later ones (all are running).
+constexpr int64_t kArriveTicks = 500000;   // 5 ms
+constexpr int64_t kWaitTicks = 20000000;   // 200 ms
+
+__device__ inline void ll_store(uint64_t* cell, uint32_t seq, double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v), s = static_cast<uint64_t>(seq) << 32;
+  __hip_atomic_store(cell, s | (b & 0xffffffffu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(cell + 1, s | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// False when the time is over.
+__device__ inline bool ll_wait(const uint64_t* cell, uint32_t seq, int64_t ticks, double& v) {
+  const int64_t until = wall_clock64() + ticks;
+  for (;;) {
+#pragma unroll 1
+    for (int tries = 0; tries < 64; ++tries) {
+      const uint64_t a = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t b = __hip_atomic_load(cell + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((a >> 32) == seq && (b >> 32) == seq) {
+        v = __builtin_bit_cast(double, (b << 32) | (a & 0xffffffffu));
+        return true;
+      }
+    }
+    if (wall_clock64() > until) return false;
+  }
+}
+
+template <typename T>
+__device__ inline T lane_value(T v, int lane) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+  } else {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), lane);
+    return __builtin_bit_cast(T, (static_cast<uint64_t>(hi) << 32) | lo);
+  }
+}
+
+// NB: frames in registers (n <= NB); NT: threads, 256 per tile.
+template <typename T, int NB, int NT>
+__global__ void __launch_bounds__(NT)
+k_resident(const SolveDesc d, const ResidentBuf rb) {
+  constexpr int NMAX = NB <= 16 ? 16 : 32;
+  constexpr int LD = eig_ld(NMAX);
+  constexpr int TPW = NT / 256;
+  constexpr int NB4 = (NB + 3) / 4 * 4;
+  constexpr int LDT = kTile + 1;
+  constexpr size_t kTileBytes = sizeof(T) * NB4 * LDT;
+  constexpr size_t kRedBytes = sizeof(double) * gram_red_doubles(NB);
+  constexpr size_t kQuarter = ((kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + 15) / 16 * 16;
+  constexpr int NENT = kScalars + gram_blocks(NB4 / 4) * 16;
+  constexpr int PQ = (NB * NB + 63) / 64;
+  // Where the registers do not hold X, S, Y and the eigensolve's working set,
+  // Y waits in the tile's LDS during the eigensolve and X is read again after
+  // it (from the L2 as a rule: 82 KB per CU, about 1 us).
+  constexpr bool SLIM = NT == 1024 || NB * sizeof(T) >= 128;
+  static_assert(kQuarter * TPW >= 2 * NT * sizeof(double), "exchange staging");
+  __shared__ __align__(16) unsigned char smem[kQuarter * TPW];
+  __shared__ EigLds<NMAX> eig;
+  __shared__ double wred[NT / 64][kScalars];
+  __shared__ double part[TPW][NENT];  // the tiles' partials
+  __shared__ double sums[NENT];
+  __shared__ T Ps[NB * NB];
+  __shared__ SolveState st;
+  __shared__ int s_go, s_lost;
+  __shared__ double s_tau;
+
+  const int tid = threadIdx.x, q = tid >> 8, t = tid & 255;
+  const int n = d.n, grid = gridDim.x, tpw = rb.tpw;
+  const int64_t m = d.m;
+  const int tile = blockIdx.x * tpw + q;
+  const bool act = q < tpw && tile < d.tiles;  // uniform over the 256 threads of a tile
+  const uint32_t p = static_cast<uint32_t>(tile) * kTile + t;
+  const bool valid = act && p < m;
+  T* const tileA = reinterpret_cast<T*>(smem + kQuarter * q);
+  double* const vals = reinterpret_cast<double*>(smem);
+  double* const gsum = vals + NT;
+
+#ifdef RPCA_TRACE
+  int64_t tprev = 0;
+#define RES_MARK(i)                       \
+  do {                                    \
+    if (threadIdx.x == 0) {               \
+      const int64_t tnow_ = RPCA_NOW();   \
+      if (i >= 0) st.trace[i] += tnow_ - tprev; \
+      tprev = tnow_;                      \
+    }                                     \
+  } while (0)
+#else
+#define RES_MARK(i) \
+  do {              \
+  } while (0)
+#endif
+  // LDS matrices zero outside n x n, V the identity
+  for (int i = tid; i < 2 * NMAX * LD; i += NT) {
+    (&eig.G[0][0])[i] = 0.0;
+    (&eig.V[0][0])[i] = 0.0;
+  }
+  if (tid == 0) {
+    SolveState z{};
+    st = z;
+    s_lost = 0;
+  }
+  __syncthreads();
+  if (tid < n) eig.V[0][tid * LD + tid] = 1.0;
+
+  const int nblk = gram_blocks((n + 3) >> 2), nent = kScalars + nblk * 16;
+  const int C = gram_chunks(nblk), Gq = gram_lane_group(C), Q = C / Gq;
+
+  // The tile in LDS (A', frame-major) and the scalars -> sums over the solve
+  // (false: gave up).
+  uint32_t seq = 0;
+  auto exchange = [&](double r2, double s1, double s2, double nf) {
+    ++seq;
+    int tid = threadIdx.x;  // not hoisted out of the iterations, as in eig_core
+    asm volatile("" : "+v"(tid));
+    const int q = tid >> 8, t = tid & 255;
+    const int gblk = t / C, gc = t - gblk * C;
+    const bool gact = act && gblk < nblk;
+    const int bj = gact ? packed_col(gblk) : 0, bi = gact ? gblk - bj * (bj + 1) / 2 : 0;
+    T* const tileA = reinterpret_cast<T*>(smem + kQuarter * q);
+    double* const red = reinterpret_cast<double*>(smem + kQuarter * q);
+    double gacc[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) gacc[e] = 0.0;
+    __syncthreads();
+    if (gact) {
+      const T* u = tileA + (4 * bi) * LDT;
+      const T* v = tileA + (4 * bj) * LDT;
+      for (int r = gc; r < kTile; r += C) {
+        double ue[4], vf[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ue[e] = static_cast<double>(u[e * LDT + r]);
+          vf[e] = static_cast<double>(v[e * LDT + r]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int f = 0; f < 4; ++f) gacc[e * 4 + f] = fma(ue[e], vf[f], gacc[e * 4 + f]);
+      }
+    }
+    __syncthreads();
+    RES_MARK(2);
+    double sc[kScalars] = {r2, s1, s2, nf};
+#pragma unroll
+    for (int s = 0; s < kScalars; ++s) sc[s] = wave_sum(sc[s]);
+    if ((tid & 63) == 0) {
+#pragma unroll
+      for (int s = 0; s < kScalars; ++s) wred[tid >> 6][s] = sc[s];
+    }
+    if (Gq >= 2) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) gacc[e] += quad_swap<kQuadXor1>(gacc[e]);
+      if (Gq == 4) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) gacc[e] += quad_swap<kQuadXor2>(gacc[e]);
+      }
+    }
+    if (gact && (gc & (Gq - 1)) == 0) {
+      double* dst = red + (gblk * Q + gc / Gq) * kRedLd;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) dst[e] = gacc[e];
+    }
+    __syncthreads();
+    for (int idx = t; idx < nblk * 16; idx += 256) {
+      double s = 0.0;
+      if (act) {
+        const double* src = red + (idx >> 4) * Q * kRedLd + (idx & 15);
+#pragma unroll 4
+        for (int c = 0; c < Q; ++c) s += src[c * kRedLd];
+      }
+      part[q][kScalars + idx] = s;
+    }
+    if (t < kScalars) {
+      double s = wred[4 * q][t];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) s += wred[4 * q + w][t];
+      part[q][t] = act ? s : 0.0;
+    }
+    __syncthreads();
+    // 1. this workgroup's tiles (missing ones are zero), summed as quads are
+    for (int e = tid; e < nent; e += NT) {
+      double v = part[0][e];
+      if constexpr (TPW >= 2) {
+        if (tpw >= 2) v += part[1][e];
+      }
+      if constexpr (TPW == 4) {
+        if (tpw == 4) v += part[2][e] + part[3][e];
+      }
+      ll_store(rb.parts + 2 * (static_cast<size_t>(e) * grid + blockIdx.x), seq, v);
+    }
+    RES_MARK(3);
+    // 2. entries blockIdx.x, blockIdx.x + grid, ...: `per` of them at a time
+    const int64_t ticks = seq == 1 ? kArriveTicks : kWaitTicks;
+    const int per = NT >> rb.ushift, groups = (d.tiles + kGroup - 1) / kGroup, upad = 1 << rb.ushift;
+    bool lost = false;
+    for (int base = blockIdx.x; base < nent; base += grid * per) {
+      const int el = tid >> rb.ushift, un = tid & (upad - 1);
+      const int e = base + grid * el;
+      double v = 0.0;
+      if (e < nent && un < grid)
+        lost = !ll_wait(rb.parts + 2 * (static_cast<size_t>(e) * grid + un), seq, ticks, v) || lost;
+      __syncthreads();  // past the reads of the staging area (red, vals)
+      vals[tid] = v;
+      __syncthreads();
+      for (int i = tid; i < per * groups; i += NT) {
+        const int l = i / groups, g = i - l * groups;
+        const double* uv = vals + (l << rb.ushift);
+        const int cnt = min(kGroup, d.tiles - g * kGroup);  // slots of the group
+        double s = 0.0;
+        for (int k = 0; k < kGroup && k < cnt; k += 4) {  // quads of slots, in order
+          const int u0 = (g * kGroup + k) / tpw;
+          auto unit = [&](int u) { return u < upad ? uv[u] : 0.0; };
+          const double quad = tpw == 4   ? unit(u0)
+                              : tpw == 2 ? unit(u0) + unit(u0 + 1)
+                                         : (unit(u0) + unit(u0 + 1)) + (unit(u0 + 2) + unit(u0 + 3));
+          s = k == 0 ? quad : s + quad;
+        }
+        gsum[i] = s;
+      }
+      __syncthreads();
+      if (tid < per && base + grid * tid < nent) {
+        double s = 0.0;
+        for (int g = 0; g < groups; ++g) s += gsum[tid * groups + g];
+        ll_store(rb.sums + 2 * (base + grid * tid), seq, s);
+      }
+    }
+    RES_MARK(4);
+    // 3. all sums
+    for (int e = tid; e < nent; e += NT) {
+      double v = 0.0;
+      lost = !ll_wait(rb.sums + 2 * e, seq, ticks, v) || lost;
+      sums[e] = v;
+    }
+    if (lost) s_lost = 1;
+    __syncthreads();
+    RES_MARK(5);
+    return s_lost == 0;
+  };
+  // Control step on this workgroup's copy of the state; the Gram into LDS.
+  auto control = [&](int kd) {
+    for (int idx = tid; idx < nblk * 16; idx += NT) {
+      const int blk = idx >> 4, e = idx & 15;
+      const int cj = packed_col(blk), ci = blk - cj * (cj + 1) / 2;
+      const int i = 4 * ci + (e >> 2), j = 4 * cj + (e & 3);
+      if (i < n && j < n) {
+        const double v = sums[kScalars + idx];
+        eig.G[0][i * LD + j] = v;
+        eig.G[0][j * LD + i] = v;
+      }
+    }
+    if (tid == 0) {
+      double tau = 0.0;
+      s_go = control_step(d, &st, sums, kd, st.nXF2, st.tau, tau);
+      s_tau = tau;
+    }
+    __syncthreads();
+    return s_go != 0;
+  };
+
+  // Rows of X; norms and Gram of X (k_stream, init)
+  const gptr<const T> X = as_global<T>(d.X);
+  T x[NB], s[NB], y[NB];
+  double s1 = 0.0, s2 = 0.0, nf = 0.0;
+#pragma unroll
+  for (int j = 0; j < NB4; ++j) {
+    T v = 0;
+    if (j < n && valid) v = (X + static_cast<size_t>(j) * m)[p];
+    const double xd = static_cast<double>(v);
+    s1 += fabs(xd);
+    s2 = fma(xd, xd, s2);
+    nf += finite_val(v) ? 0.0 : 1.0;
+    if (act) tileA[j * LDT + t] = v;
+    if (j < NB) {
+      x[j] = v;
+      s[j] = 0;
+      y[j] = 0;
+    }
+  }
+  bool alive = exchange(0.0, s1, s2, nf);
+  bool go = false;
+  if (alive) {
+    go = control(0);
+    if (!go && st.warm_stage == 1 && !st.done) {
+      // given start: Gram of A_1 = X - S0 + Y0/mu (k_stream, warm)
+      const T imu = static_cast<T>(st.imu);
+      const gptr<const T> S0 = as_global<T>(d.S0), Y0 = as_global<T>(d.Y0);
+#pragma unroll
+      for (int j = 0; j < NB4; ++j) {
+        T a = 0;
+        if (j < NB && j < n && valid) {
+          const size_t col = static_cast<size_t>(j) * m;
+          if (d.S0) s[j] = (S0 + col)[p];
+          if (d.Y0) y[j] = (Y0 + col)[p];
+          a = fma(y[j], imu, x[j] - s[j]);
+        }
+        if (act) tileA[j * LDT + t] = a;
+      }
+      alive = exchange(0.0, 0.0, 0.0, 0.0);
+      if (alive) go = control(0);
+    }
+  }
+
+  const gptr<T> L = as_global<T>(d.Lout);
+  int kd = 0;
+  while (alive && go) {
+    int sweeps = 0;
+    RES_MARK(-1);
+    if constexpr (SLIM) {
+      if (act) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) tileA[j * LDT + t] = y[j];
+      }
+    }
+    const int cur = eig_core<T, NMAX, NT>(
+        eig, n, kd > 0, (kd & (kOrthPeriod - 1)) == 0, s_tau, sweeps,
+        [&](int i, int j, double v) {
+          if (j < NB) {
+            Ps[i * NB + j] = static_cast<T>(v);
+            Ps[j * NB + i] = static_cast<T>(v);
+          }
+        },
+        [](int) {});
+    __syncthreads();
+    if (cur == 1) {  // V back to copy 0
+      for (int i = tid; i < NMAX * LD; i += NT) eig.V[0][i] = eig.V[1][i];
+    }
+    if (tid == 0) {
+      int rank = 0;
+      for (int k = 0; k < n; ++k) rank += eig.w[k] != 0.0 ? 1 : 0;
+      st.rank = rank;
+      st.sweeps = sweeps;
+      st.sweeps_total += sweeps;
+      st.iter = kd + 1;
+    }
+    ++kd;
+    RES_MARK(0);
+    // Update of the rows (k_stream, update).  P comes from one register per 64
+    // entries, a lane's value at a time.  L_k goes out where this iteration may
+    // be the last.
+    T pv[PQ];
+#pragma unroll
+    for (int i = 0; i < PQ; ++i) {
+      const int idx = (tid & 63) + 64 * i;
+      pv[i] = Ps[idx < NB * NB ? idx : 0];
+    }
+    const T mu = static_cast<T>(st.mu), imu = static_cast<T>(st.imu), gam = static_cast<T>(st.gamma);
+    const bool out = d.tol > 0.0 || kd >= d.maxit;
+    double r2 = 0.0;
+    if (act) {
+      if constexpr (SLIM) {
+        const gptr<const T> Xa = opaque(X);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          x[j] = 0;
+          if (j < n && valid) x[j] = (Xa + static_cast<size_t>(j) * m)[p];
+          y[j] = tileA[j * LDT + t];
+        }
+      }
+      T a[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) a[j] = fma(y[j], imu, x[j] - s[j]);
+#pragma unroll
+      for (int j = 0; j < NB4; ++j) {
+        T apj = 0;
+        if (j < NB && j < n) {
+          T l = 0;
+#pragma unroll
+          for (int i = 0; i < NB; ++i) l = fma(a[i], lane_value(pv[(j * NB + i) >> 6], (j * NB + i) & 63), l);
+          const T tt = fma(y[j], imu, x[j]) - l;
+          const T sn = tt - clamp_sym(tt, gam);
+          const T z = (x[j] - l) - sn;
+          const T yn = fma(mu, z, y[j]);
+          const double zd = static_cast<double>(z);
+          r2 = fma(zd, zd, r2);
+          apj = valid ? fma(yn, imu, x[j] - sn) : T(0);
+          s[j] = sn;
+          y[j] = yn;
+          if (out && valid) (L + static_cast<size_t>(j) * m)[p] = l;
+        }
+        tileA[j * LDT + t] = apj;
+      }
+    }
+    RES_MARK(1);
+    alive = exchange(r2, 0.0, 0.0, 0.0);
+    if (alive) go = control(kd);
+  }
+#undef RES_MARK
+
+  if (!alive) {
+    if (tid == 0) __hip_atomic_store(rb.lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (st.status >= 0 && valid) {
+    const gptr<T> So = as_global<T>(d.Sout), Yo = as_global<T>(d.Yout);
+    const bool none = kd == 0;  // sum|X| == 0: L = S = 0 (and Y = 0)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j < n) {
+        const size_t col = static_cast<size_t>(j) * m;
+        if (none) (L + col)[p] = T(0);
+        (So + col)[p] = none ? T(0) : s[j];
+        if (d.Yout) (Yo + col)[p] = none ? T(0) : y[j];
+      }
+    }
+  }
+  if (blockIdx.x == 0 && tid == 0) *d.st = st;
+}
+
+template <typename T, int NB, int NT>
+hipError_t launch_resident_class(int grid, hipStream_t stream, const SolveDesc& d, const ResidentBuf& rb) {
+  hipLaunchKernelGGL((k_resident<T, NB, NT>), dim3(grid), dim3(NT), 0, stream, d, rb);
+  return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace rpca
