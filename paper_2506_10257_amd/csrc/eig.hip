@@ -133,7 +133,7 @@ k_eig(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
   int sweeps = 0;
   const gptr<T> Pd = as_global<T>(d.P);
   const int cur = eig_core<T, NMAX, NT>(
-      sh, n, warm, (kd & (kOrthPeriod - 1)) == 0, tau, sweeps,
+      sh, n, warm, tau, sweeps,
       [&](int i, int j, double v) {
         if (j < nb) {
           Pd[i * nb + j] = static_cast<T>(v);

@@ -13,12 +13,12 @@ constexpr int kMaxSweeps = 40;
 
 // Simultaneous rotation steps (see eig.hip).
 constexpr int kMaxSteps = 12;          // per launch; then sweeps only
-constexpr int kMaxOrth = 6;            // Newton-Schulz steps of one U
-constexpr float kOrthMax = 0.25f;      // largest |U^T U - I| entry that a step starts from
+constexpr int kMaxPasses = 100;        // steps and sweeps together
+constexpr float kOrthMax = 0.25f;      // largest |V^T V - I| entry that a step starts from
+constexpr float kRowSumMax = 0.9f;     // largest row sum of |K| (a bound of its norm) of a step
 constexpr double kTangentMax = 0.5;    // tangents are clipped here
 constexpr float kColdTangent = 0.25f;  // first launch: steps only once every tangent is below
 constexpr float kWideFourth = 0.02f;   // wide solves: above this tangent, U to fourth order
-constexpr int kOrthPeriod = 8;         // launches between Newton-Schulz steps on V
 
 // Bound on the second-order error of an entry of P: for FP32 solves below the
 // rounding of P's own entries (and that of the diagonal Z this replaces, whose
@@ -34,7 +34,7 @@ template <>
 struct PTarget<float> {
   static constexpr float value = 5.0e-9f;
 };
-// Entries of |U^T U - I| that need no (further) Newton-Schulz step.
+// Entries of |V^T V - I| below which V counts as orthogonal.
 template <typename T>
 struct OrthGoal;
 template <>

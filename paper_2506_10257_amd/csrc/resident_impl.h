@@ -70,15 +70,71 @@ __device__ inline bool ll_wait(const uint64_t* cell, uint32_t seq, int64_t ticks
   }
 }
 
-template <typename T>
-__device__ inline T lane_value(T v, int lane) {
+// l[k] += p_k a for k < BLK, where lane k of each row of 16 lanes of p holds
+// p_k: a broadcast inside the FMA (DPP row_newbcast), so the projector costs no
+// instruction beside the FMAs.  With scalar loads, as in k_stream, the scalar
+// cache would have to be invalidated every iteration; through v_readlane the
+// update took 10.4 us at 512 x 512 x 20.  (s_nop: two wait states between a
+// write of p and its DPP use.)
+template <int BLK, typename T>
+__device__ inline void fma_row(T* l, T p, T a) {
+  static_assert(BLK == 8 || BLK == 10, "columns per row of P");
   if constexpr (sizeof(T) == 4) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+    if constexpr (BLK == 8) {
+      asm("s_nop 1\n\t"
+          "v_fmac_f32_dpp %0, %8, %9 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %8, %9 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %8, %9 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %3, %8, %9 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %4, %8, %9 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %5, %8, %9 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %6, %8, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %7, %8, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7])
+          : "v"(p), "v"(a));
+    } else {
+      asm("s_nop 1\n\t"
+          "v_fmac_f32_dpp %0, %10, %11 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %1, %10, %11 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %2, %10, %11 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %3, %10, %11 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %4, %10, %11 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %5, %10, %11 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %6, %10, %11 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %7, %10, %11 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %8, %10, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f32_dpp %9, %10, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7]), "+v"(l[8]), "+v"(l[9])
+          : "v"(p), "v"(a));
+    }
   } else {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), lane);
-    return __builtin_bit_cast(T, (static_cast<uint64_t>(hi) << 32) | lo);
+    if constexpr (BLK == 8) {
+      asm("s_nop 1\n\t"
+          "v_fmac_f64_dpp %0, %8, %9 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %1, %8, %9 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %2, %8, %9 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %3, %8, %9 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %4, %8, %9 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %5, %8, %9 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %6, %8, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %7, %8, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7])
+          : "v"(p), "v"(a));
+    } else {
+      asm("s_nop 1\n\t"
+          "v_fmac_f64_dpp %0, %10, %11 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %1, %10, %11 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %2, %10, %11 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %3, %10, %11 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %4, %10, %11 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %5, %10, %11 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %6, %10, %11 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %7, %10, %11 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %8, %10, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %9, %10, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7]), "+v"(l[8]), "+v"(l[9])
+          : "v"(p), "v"(a));
+    }
   }
 }
 
@@ -95,8 +151,9 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
   constexpr size_t kRedBytes = sizeof(double) * gram_red_doubles(NB);
   constexpr size_t kQuarter = ((kTileBytes > kRedBytes ? kTileBytes : kRedBytes) + 15) / 16 * 16;
   constexpr int NENT = kScalars + gram_blocks(NB4 / 4) * 16;
-  constexpr int PQ = (NB * NB + 63) / 64;
-  // Where the registers do not hold X, S, Y and the eigensolve's working set,
+  constexpr int BLK = NB % 10 == 0 ? 10 : 8;  // columns of P per row of 16 lanes
+  constexpr int NBL = NB / BLK;
+  // Where the registers do not hold X, Y, A and the eigensolve's working set,
   // Y waits in the tile's LDS during the eigensolve and X is read again after
   // it (from the L2 as a rule: 82 KB per CU, about 1 us).
   constexpr bool SLIM = NT == 1024 || NB * sizeof(T) >= 128;
@@ -106,7 +163,7 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
   __shared__ double wred[NT / 64][kScalars];
   __shared__ double part[TPW][NENT];  // the tiles' partials
   __shared__ double sums[NENT];
-  __shared__ T Ps[NB * NB];
+  __shared__ T Ps[NB * NBL * 16];  // P(i, j) at ((i * NBL) + j / BLK) * 16 + j % BLK
   __shared__ SolveState st;
   __shared__ int s_go, s_lost;
   __shared__ double s_tau;
@@ -123,7 +180,7 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
   double* const gsum = vals + NT;
 
 #ifdef RPCA_TRACE
-  int64_t tprev = 0;
+  int64_t tprev = RPCA_NOW();
 #define RES_MARK(i)                       \
   do {                                    \
     if (threadIdx.x == 0) {               \
@@ -156,7 +213,7 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
   // The tile in LDS (A', frame-major) and the scalars -> sums over the solve
   // (false: gave up).
   uint32_t seq = 0;
-  auto exchange = [&](double r2, double s1, double s2, double nf) {
+  auto exchange = [&](auto norms, double r2, double s1, double s2, double nf) {
     ++seq;
     int tid = threadIdx.x;  // not hoisted out of the iterations, as in eig_core
     asm volatile("" : "+v"(tid));
@@ -188,9 +245,14 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
     }
     __syncthreads();
     RES_MARK(2);
+    // r2 is zero in the first pass, the norms of X in all others
     double sc[kScalars] = {r2, s1, s2, nf};
+    if constexpr (decltype(norms)::value) {
 #pragma unroll
-    for (int s = 0; s < kScalars; ++s) sc[s] = wave_sum(sc[s]);
+      for (int s = 1; s < kScalars; ++s) sc[s] = wave_sum(sc[s]);
+    } else {
+      sc[0] = wave_sum(sc[0]);
+    }
     if ((tid & 63) == 0) {
 #pragma unroll
       for (int s = 0; s < kScalars; ++s) wred[tid >> 6][s] = sc[s];
@@ -247,28 +309,40 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
       double v = 0.0;
       if (e < nent && un < grid)
         lost = !ll_wait(rb.parts + 2 * (static_cast<size_t>(e) * grid + un), seq, ticks, v) || lost;
-      __syncthreads();  // past the reads of the staging area (red, vals)
+      // (the staging area's last reads: red before the barrier above, or this loop)
+      if (base != static_cast<int>(blockIdx.x)) __syncthreads();
       vals[tid] = v;
       __syncthreads();
       for (int i = tid; i < per * groups; i += NT) {
         const int l = i / groups, g = i - l * groups;
         const double* uv = vals + (l << rb.ushift);
         const int cnt = min(kGroup, d.tiles - g * kGroup);  // slots of the group
-        double s = 0.0;
-        for (int k = 0; k < kGroup && k < cnt; k += 4) {  // quads of slots, in order
-          const int u0 = (g * kGroup + k) / tpw;
+        double quad[kGroup / 4];
+#pragma unroll
+        for (int k = 0; k < kGroup / 4; ++k) {  // every read before the first sum
+          const int u0 = (g * kGroup + 4 * k) / tpw;
           auto unit = [&](int u) { return u < upad ? uv[u] : 0.0; };
-          const double quad = tpw == 4   ? unit(u0)
-                              : tpw == 2 ? unit(u0) + unit(u0 + 1)
-                                         : (unit(u0) + unit(u0 + 1)) + (unit(u0 + 2) + unit(u0 + 3));
-          s = k == 0 ? quad : s + quad;
+          quad[k] = tpw == 4   ? unit(u0)
+                    : tpw == 2 ? unit(u0) + unit(u0 + 1)
+                               : (unit(u0) + unit(u0 + 1)) + (unit(u0 + 2) + unit(u0 + 3));
         }
+        double s = quad[0];
+#pragma unroll
+        for (int k = 1; k < kGroup / 4; ++k)  // quads of slots, in order
+          if (4 * k < cnt) s += quad[k];
         gsum[i] = s;
       }
       __syncthreads();
       if (tid < per && base + grid * tid < nent) {
         double s = 0.0;
-        for (int g = 0; g < groups; ++g) s += gsum[tid * groups + g];
+        for (int g0 = 0; g0 < groups; g0 += 16) {  // sixteen reads in flight
+          double v[16];
+#pragma unroll
+          for (int k = 0; k < 16; ++k) v[k] = g0 + k < groups ? gsum[tid * groups + g0 + k] : 0.0;
+#pragma unroll
+          for (int k = 0; k < 16; ++k)
+            if (g0 + k < groups) s += v[k];
+        }
         ll_store(rb.sums + 2 * (base + grid * tid), seq, s);
       }
     }
@@ -305,51 +379,69 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
     return s_go != 0;
   };
 
+  // Column by column through a running address (m is a scalar; the columns'
+  // bases would take two scalar registers each).  Rows past m and frames past n
+  // hold zeros, and zeros stay zeros through the update, so it needs no guards.
+  auto columns = [&](auto base, auto&& f) __attribute__((always_inline)) {
+    if (valid) {
+      auto at = opaque(base) + p;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        if (j < n) {
+          f(j, at);
+          at += m;
+        }
+      }
+    }
+  };
+
   // Rows of X; norms and Gram of X (k_stream, init)
   const gptr<const T> X = as_global<T>(d.X);
-  T x[NB], s[NB], y[NB];
+  // (s goes out at the end only: the update needs x, y and a)
+  T x[NB], s[NB], y[NB], a[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    x[j] = 0;
+    s[j] = 0;
+    y[j] = 0;
+  }
+  columns(X, [&](int j, auto at) { x[j] = *at; });
   double s1 = 0.0, s2 = 0.0, nf = 0.0;
 #pragma unroll
   for (int j = 0; j < NB4; ++j) {
-    T v = 0;
-    if (j < n && valid) v = (X + static_cast<size_t>(j) * m)[p];
+    const T v = j < NB ? x[j] : T(0);
     const double xd = static_cast<double>(v);
     s1 += fabs(xd);
     s2 = fma(xd, xd, s2);
     nf += finite_val(v) ? 0.0 : 1.0;
     if (act) tileA[j * LDT + t] = v;
-    if (j < NB) {
-      x[j] = v;
-      s[j] = 0;
-      y[j] = 0;
-    }
   }
-  bool alive = exchange(0.0, s1, s2, nf);
+  bool alive = exchange(std::true_type{}, 0.0, s1, s2, nf);
   bool go = false;
   if (alive) {
     go = control(0);
     if (!go && st.warm_stage == 1 && !st.done) {
       // given start: Gram of A_1 = X - S0 + Y0/mu (k_stream, warm)
       const T imu = static_cast<T>(st.imu);
-      const gptr<const T> S0 = as_global<T>(d.S0), Y0 = as_global<T>(d.Y0);
+      if (d.S0) columns(as_global<T>(d.S0), [&](int j, auto at) { s[j] = *at; });
+      if (d.Y0) columns(as_global<T>(d.Y0), [&](int j, auto at) { y[j] = *at; });
+      if (act) {
 #pragma unroll
-      for (int j = 0; j < NB4; ++j) {
-        T a = 0;
-        if (j < NB && j < n && valid) {
-          const size_t col = static_cast<size_t>(j) * m;
-          if (d.S0) s[j] = (S0 + col)[p];
-          if (d.Y0) y[j] = (Y0 + col)[p];
-          a = fma(y[j], imu, x[j] - s[j]);
-        }
-        if (act) tileA[j * LDT + t] = a;
+        for (int j = 0; j < NB4; ++j) tileA[j * LDT + t] = j < NB ? fma(y[j], imu, x[j] - s[j]) : T(0);
       }
-      alive = exchange(0.0, 0.0, 0.0, 0.0);
+      alive = exchange(std::false_type{}, 0.0, 0.0, 0.0, 0.0);
       if (alive) go = control(0);
     }
   }
 
   const gptr<T> L = as_global<T>(d.Lout);
   int kd = 0;
+  {
+    // A_1; later ones are what the update puts into the tile (same operations)
+    const T imu = static_cast<T>(st.imu);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) a[j] = fma(y[j], imu, x[j] - s[j]);
+  }
   while (alive && go) {
     int sweeps = 0;
     RES_MARK(-1);
@@ -360,11 +452,11 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
       }
     }
     const int cur = eig_core<T, NMAX, NT>(
-        eig, n, kd > 0, (kd & (kOrthPeriod - 1)) == 0, s_tau, sweeps,
+        eig, n, kd > 0, s_tau, sweeps,
         [&](int i, int j, double v) {
           if (j < NB) {
-            Ps[i * NB + j] = static_cast<T>(v);
-            Ps[j * NB + i] = static_cast<T>(v);
+            Ps[(i * NBL + j / BLK) * 16 + j % BLK] = static_cast<T>(v);
+            Ps[(j * NBL + i / BLK) * 16 + i % BLK] = static_cast<T>(v);
           }
         },
         [](int) {});
@@ -382,54 +474,72 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
     }
     ++kd;
     RES_MARK(0);
-    // Update of the rows (k_stream, update).  P comes from one register per 64
-    // entries, a lane's value at a time.  L_k goes out where this iteration may
-    // be the last.
-    T pv[PQ];
-#pragma unroll
-    for (int i = 0; i < PQ; ++i) {
-      const int idx = (tid & 63) + 64 * i;
-      pv[i] = Ps[idx < NB * NB ? idx : 0];
-    }
+    // Update of the rows (k_stream, update), all columns of L side by side.  L_k
+    // goes out where this iteration may be the last.
     const T mu = static_cast<T>(st.mu), imu = static_cast<T>(st.imu), gam = static_cast<T>(st.gamma);
     const bool out = d.tol > 0.0 || kd >= d.maxit;
     double r2 = 0.0;
+    if constexpr (SLIM) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {  // (set by every thread: dead during the eigensolve)
+        x[j] = 0;
+        y[j] = 0;
+      }
+      columns(X, [&](int j, auto at) { x[j] = *at; });
+      if (act) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) y[j] = tileA[j * LDT + t];
+      }
+    }
     if (act) {
-      if constexpr (SLIM) {
-        const gptr<const T> Xa = opaque(X);
+      T l[NB], pr[2][NBL];  // a row of P is read while the one before it is used
+      const T* const Pt = Ps + (t & 15);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) l[j] = 0;
+#pragma unroll
+      for (int c = 0; c < NBL; ++c) pr[0][c] = Pt[c * 16];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (i + 1 < NB) {
+#pragma unroll
+          for (int c = 0; c < NBL; ++c) pr[(i + 1) & 1][c] = Pt[((i + 1) * NBL + c) * 16];
+        }
+#pragma unroll
+        for (int c = 0; c < NBL; ++c) fma_row<BLK>(l + c * BLK, pr[i & 1][c], a[i]);
+        if constexpr (NT == 1024) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const T tt = fma(y[j], imu, x[j]) - l[j];
+        const T sn = tt - clamp_sym(tt, gam);
+        const T z = (x[j] - l[j]) - sn;
+        const T yn = fma(mu, z, y[j]);
+        const double zd = static_cast<double>(z);
+        r2 = fma(zd, zd, r2);
+        a[j] = fma(yn, imu, x[j] - sn);
+        s[j] = sn;
+        y[j] = yn;
+        tileA[j * LDT + t] = a[j];
+        // 128 registers: not more than two columns at a time
+        if constexpr (NT == 1024)
+          if (j & 1) __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int j = NB; j < NB4; ++j) tileA[j * LDT + t] = 0;
+      // (written out: captured by a lambda, l becomes one 32-register tuple)
+      if (out && valid) {
+        gptr<T> at = opaque(L) + p;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          x[j] = 0;
-          if (j < n && valid) x[j] = (Xa + static_cast<size_t>(j) * m)[p];
-          y[j] = tileA[j * LDT + t];
+          if (j < n) {
+            *at = l[j];
+            at += m;
+          }
         }
-      }
-      T a[NB];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) a[j] = fma(y[j], imu, x[j] - s[j]);
-#pragma unroll
-      for (int j = 0; j < NB4; ++j) {
-        T apj = 0;
-        if (j < NB && j < n) {
-          T l = 0;
-#pragma unroll
-          for (int i = 0; i < NB; ++i) l = fma(a[i], lane_value(pv[(j * NB + i) >> 6], (j * NB + i) & 63), l);
-          const T tt = fma(y[j], imu, x[j]) - l;
-          const T sn = tt - clamp_sym(tt, gam);
-          const T z = (x[j] - l) - sn;
-          const T yn = fma(mu, z, y[j]);
-          const double zd = static_cast<double>(z);
-          r2 = fma(zd, zd, r2);
-          apj = valid ? fma(yn, imu, x[j] - sn) : T(0);
-          s[j] = sn;
-          y[j] = yn;
-          if (out && valid) (L + static_cast<size_t>(j) * m)[p] = l;
-        }
-        tileA[j * LDT + t] = apj;
       }
     }
     RES_MARK(1);
-    alive = exchange(r2, 0.0, 0.0, 0.0);
+    alive = exchange(std::false_type{}, r2, 0.0, 0.0, 0.0);
     if (alive) go = control(kd);
   }
 #undef RES_MARK
@@ -438,18 +548,11 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
     if (tid == 0) __hip_atomic_store(rb.lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  if (st.status >= 0 && valid) {
-    const gptr<T> So = as_global<T>(d.Sout), Yo = as_global<T>(d.Yout);
+  if (st.status >= 0) {
     const bool none = kd == 0;  // sum|X| == 0: L = S = 0 (and Y = 0)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j < n) {
-        const size_t col = static_cast<size_t>(j) * m;
-        if (none) (L + col)[p] = T(0);
-        (So + col)[p] = none ? T(0) : s[j];
-        if (d.Yout) (Yo + col)[p] = none ? T(0) : y[j];
-      }
-    }
+    if (none) columns(L, [&](int, auto at) { *at = T(0); });
+    columns(as_global<T>(d.Sout), [&](int j, auto at) { *at = none ? T(0) : s[j]; });
+    if (d.Yout) columns(as_global<T>(d.Yout), [&](int j, auto at) { *at = none ? T(0) : y[j]; });
   }
   if (blockIdx.x == 0 && tid == 0) *d.st = st;
 }
