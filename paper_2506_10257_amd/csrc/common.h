@@ -126,6 +126,12 @@ constexpr int kWideCtlDoubles = 32;
 struct WideCtl {
   int32_t booked;  // the iteration whose P the steps wrote last (0: none)
   int32_t vsel;    // which of the three V buffers holds V
+  // the steps' workgroups of one launch; zero between launches
+  uint32_t arrived;                  // meetings, counted by workgroup
+  uint32_t lost;                     // a workgroup gave up waiting
+  uint32_t go;                       // the control step's answer
+  uint32_t mx[kWideSteps + 1][4];    // maxima over a step's pairs
+  double tau;
 };
 static_assert(sizeof(WideCtl) <= kWideCtlDoubles * sizeof(double), "control block size");
 inline int wide_class(int n) { return n <= kEigWideMaxN ? kEigWideMaxN : kEigHugeMaxN; }

@@ -253,7 +253,7 @@ __device__ inline double sqrt_or_zero(double d) { return d > kTiny2 ? d * rsqrt_
 struct WideEig {
   WideCtl* ctl;
   double *G, *W, *S, *K, *T, *U, *C, *Z;
-  double* VT[2];  // V^T of the even and of the odd steps
+  double* VT0;  // V^T of the even steps, then of the odd ones
   double* V0;   // the solve's V buffer
   double* V12;  // the two others
   size_t q;     // nb x nb
@@ -272,14 +272,14 @@ struct WideEig {
     C = p + 6 * q;
     Z = p + 7 * q;
     V12 = p + 8 * q;
-    VT[0] = p + 10 * q;
-    VT[1] = p + 11 * q;
+    VT0 = p + 10 * q;
     V0 = d.V;
   }
   // V after s steps from buffer v0: the previous iteration's V stays where it
   // is (the Jacobi kernel starts from it if the steps fail), the steps
   // alternate between the other two buffers.
   __device__ static int vsel(int v0, int s) { return s == 0 ? v0 : (v0 + (s & 1 ? 1 : 2)) % 3; }
+  __device__ double* vt(int b) const { return VT0 + b * q; }
   __device__ double* v(int b) const { return b == 0 ? V0 : V12 + (b - 1) * q; }
 };
 

@@ -1,5 +1,5 @@
 // Warm-started eigensolve of windows of 65 to 144 frames by simultaneous
-// rotation steps, one workgroup per solve.
+// rotation steps, by a team of workgroups per solve.
 //
 // The method is that of the simultaneous steps in eig.hip: all pairs of the
 // nearly diagonal G~ = V^T G V are rotated at once through matrix products, and
@@ -23,9 +23,18 @@
 // rotated dense clusters, or more than kWideSteps steps) the Jacobi kernel
 // (eig_wide.hip), launched next, runs sweeps from the previous iteration's V.
 //
-// Bound: a product is 2 nb^3 FP64 operations on one CU (307 GFLOP/s: 19 us at
-// 144 frames, 9 us at 112), and a solve takes about 15 of them per iteration;
-// a Jacobi sweep is 131 (99) dependent rounds, 500 (230) us at 132 (100).
+// Bound: with one workgroup, by its CU's matrix cores: a product is 2 nb^3 FP64
+// operations (307 GFLOP/s: 19 us at 144 frames, 9 us at 112), a launch has about
+// ten, 220 (480) us at 100 (132) frames.  A team has one wave per 16 x 16 block
+// of the widest phase: then a phase is one block's latency and the meeting after
+// it, 6 to 8 us, and a launch 100 (125) us.  A launch of several solves divides
+// kTeamGroups workgroups between them.  The blocks are computed alike however
+// many workgroups there are, so the results have the same bits.
+//
+// A workgroup waits for its team at every meeting, for kTeamTicks at most; then
+// it gives up, all others follow, and the Jacobi kernel does the iteration.
+#include <algorithm>
+
 #include "common.h"
 #include "eig_common.h"
 #include "launch.h"
@@ -39,6 +48,80 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int kStepThreads = 512;
 constexpr int kStepWaves = kStepThreads / 64;
+
+// Workgroups of a team read what others of it wrote within the launch: such
+// loads and stores go to the memory that all CUs share (relaxed atomics, agent
+// scope), past the L2 of the CU's own XCD.
+template <bool TEAM>
+__device__ inline double ld(gptr<const double> p) {
+  if constexpr (TEAM) return __hip_atomic_load((const double*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+template <bool TEAM, typename T>
+__device__ inline void st_to(gptr<T> p, T v) {
+  if constexpr (TEAM) __hip_atomic_store((T*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+
+// All workgroups of a team, each at its meeting number `meeting` (1, 2, ...):
+// what any of them stored before is seen by all after.  False when one of them
+// did not come in time (kTeamTicks of the 100 MHz wall clock).
+constexpr int64_t kTeamTicks = 20000000;  // 200 ms
+template <bool TEAM>
+__device__ inline bool meet(WideCtl* ctl, unsigned meeting, int* s_ok) {
+  if constexpr (!TEAM) {
+    __syncthreads();
+    return true;
+  } else {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's stores have left
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned all = meeting * gridDim.x;
+      const int64_t until = wall_clock64() + kTeamTicks;
+      int ok = 1;
+      while (__hip_atomic_load(&ctl->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
+        if (__hip_atomic_load(&ctl->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) ok = 0;
+        if (ok && wall_clock64() > until) {
+          __hip_atomic_store(&ctl->lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ok = 0;
+        }
+        if (!ok) break;
+      }
+      *s_ok = ok;
+    }
+    __syncthreads();
+    return *s_ok != 0;
+  }
+}
+
+// Block (bi, bj) of X^T Y by one wave, every operand in flight at once (a
+// team's waves have one block each; the loads' latency is paid once).
+__device__ inline d4 block1(const double* Xp, const double* Yp, int nb, int bi, int bj) {
+  constexpr int C = kEigHugeMaxN / 16;
+  const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15, nt = nb >> 4;
+  const gptr<const double> x = as_global<double>(static_cast<const void*>(Xp + lr * nb + 16 * bi + lc));
+  const gptr<const double> y = as_global<double>(static_cast<const void*>(Yp + lr * nb + 16 * bj + lc));
+  double a[C][4], b[C][4];
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (c < nt) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        a[c][k] = ld<true>(x + (16 * c + 4 * k) * nb);
+        b[c][k] = ld<true>(y + (16 * c + 4 * k) * nb);
+      }
+    }
+  d4 s = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (c < nt) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s = __builtin_amdgcn_mfma_f64_16x16x4f64(a[c][k], b[c][k], s, 0, 0, 0);
+    }
+  return s;
+}
 
 // The 2 x 2 blocks (bi + p, bj + q) of X^T Y into s[p][q]; blocks past the last
 // row or column (or, SYM, below the diagonal) are skipped.  A operand lane l =
@@ -92,24 +175,29 @@ __device__ inline void blocks4(const double* Xp, const double* Yp, int nb, int b
   }
 }
 
-// Every block of X^T Y (SYM: the upper ones), in units of 2 x 2 blocks: the
-// units u, u + kStepWaves, ... of this wave.  `u` is advanced past the product's
-// units, so that two products with no barrier between them share the waves
-// evenly.  out(bi, bj, block) is called for each 16 x 16 block.
-template <bool SYM, typename Out>
-__device__ inline void product(int& u, const double* X, const double* Y, int nb, Out&& out) {
-  const int nt = nb >> 4, n2 = (nt + 1) >> 1;
+// Every block of X^T Y (SYM: the upper ones), in units of 2 x 2 blocks or, in a
+// team, single ones: the units u, u + nw, ... of this wave (nw: waves of the
+// solve).  `u` is advanced past the product's units, so that two products with
+// no barrier between them share the waves evenly.  out(bi, bj, block) is called
+// for each 16 x 16 block.
+template <bool TEAM, bool SYM, typename Out>
+__device__ inline void product(int& u, int nw, const double* X, const double* Y, int nb, Out&& out) {
+  const int nt = nb >> 4, n2 = TEAM ? nt : (nt + 1) >> 1;
   const int units = SYM ? n2 * (n2 + 1) / 2 : n2 * n2;
-  for (; u < units; u += kStepWaves) {
+  for (; u < units; u += nw) {
     const int uj = SYM ? packed_col(u) : u % n2, ui = SYM ? u - uj * (uj + 1) / 2 : u / n2;
-    const int bi = 2 * ui, bj = 2 * uj;
-    d4 s[2][2];
-    blocks4<SYM>(X, Y, nb, bi, bj, s);
+    if constexpr (TEAM) {
+      out(ui, uj, block1(X, Y, nb, ui, uj));
+    } else {
+      const int bi = 2 * ui, bj = 2 * uj;
+      d4 s[2][2];
+      blocks4<SYM>(X, Y, nb, bi, bj, s);
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+      for (int p = 0; p < 2; ++p)
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-        if (bi + p < nt && bj + q < nt && !(SYM && bi + p > bj + q)) out(bi + p, bj + q, s[p][q]);
+        for (int q = 0; q < 2; ++q)
+          if (bi + p < nt && bj + q < nt && !(SYM && bi + p > bj + q)) out(bi + p, bj + q, s[p][q]);
+    }
   }
   u -= units;
 }
@@ -129,51 +217,52 @@ __device__ inline d4 transposed(const d4& v, double* tb) {
   __builtin_amdgcn_wave_barrier();
   return t;
 }
-template <typename T>
+template <bool TEAM, typename T>
 __device__ inline void store_block(T* M, int nb, int bi, int bj, const d4& v) {
   const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
   const gptr<T> p = as_global<T>(static_cast<void*>(M + (16 * bi + lr) * nb + 16 * bj + lc));
 #pragma unroll
-  for (int r = 0; r < 4; ++r) p[4 * r * nb] = static_cast<T>(v[r]);
+  for (int r = 0; r < 4; ++r) st_to<TEAM>(p + 4 * r * nb, static_cast<T>(v[r]));
 }
 // Upper block (bi, bj) of a symmetric matrix h + k with h symmetric and k
 // antisymmetric (entries of h, k; k may be zero), and its mirror image h - k.
 // On the diagonal the entries above it decide both.
-template <typename T>
+template <bool TEAM, typename T>
 __device__ inline void store_mirrored(T* M, int nb, int bi, int bj, const d4& h, const d4& k, double* tb) {
   const d4 lo = transposed(h - k, tb);
   if (bi != bj) {
-    store_block(M, nb, bi, bj, h + k);
-    store_block(M, nb, bj, bi, lo);
+    store_block<TEAM>(M, nb, bi, bj, h + k);
+    store_block<TEAM>(M, nb, bj, bi, lo);
   } else {
     const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
     d4 v;
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = lr + 4 * r <= lc ? h[r] + k[r] : lo[r];
-    store_block(M, nb, bi, bj, v);
+    store_block<TEAM>(M, nb, bi, bj, v);
   }
 }
+template <bool TEAM>
 __device__ inline d4 load_block(const double* M, int nb, int bi, int bj) {
   const int l = threadIdx.x & 63, lr = l >> 4, lc = l & 15;
   const gptr<const double> p =
       as_global<double>(static_cast<const void*>(M + (16 * bi + lr) * nb + 16 * bj + lc));
   d4 v;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = p[4 * r * nb];
+  for (int r = 0; r < 4; ++r) v[r] = ld<TEAM>(p + 4 * r * nb);
   return v;
 }
 
-template <typename T>
+template <typename T, bool TEAM>
 __global__ void __launch_bounds__(kStepThreads)
 k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
   __shared__ double dg[kEigHugeMaxN], sg[kEigHugeMaxN], w[kEigHugeMaxN], sd[kEigHugeMaxN];
   __shared__ double tbuf[kStepWaves][16 * kTrLd];
   __shared__ double scal[kScalars];
   __shared__ unsigned mx[2][4];
-  __shared__ int s_go;
+  __shared__ int s_go, s_ok;
   __shared__ double s_tau;
   const int tid = threadIdx.x;
-  const SolveDesc& d = descs[ids[blockIdx.x]];
+  const SolveDesc& d = descs[ids[blockIdx.y]];
   SolveState* st = d.st;
   // a solve's first eigensolve is the Jacobi kernel's
   if (st->done || st->iter == 0) return;
@@ -181,7 +270,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   int64_t tprev = RPCA_NOW();
 #define STEP_MARK(i)                              \
   do {                                            \
-    if (tid == 0) {                               \
+    if (tid == 0 && blockIdx.x == 0) {            \
       const int64_t tnow_ = RPCA_NOW();           \
       st->trace[i] += tnow_ - tprev;              \
       tprev = tnow_;                              \
@@ -195,17 +284,23 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const WideEig e(d);
   const int n = d.n, nb = d.nb, kd = st->iter;
   double pf_nXF2 = 0.0, pf_tau = 0.0;
-  if (tid == 0) {
+  // workgroup g of the solve's team; thread and wave of the whole team
+  const int g = TEAM ? blockIdx.x : 0;
+  const int teams = TEAM ? gridDim.x : 1, nw = teams * kStepWaves, gtid = g * kStepThreads + tid;
+  unsigned meeting = 0;
+  if (tid == 0 && g == 0) {
     pf_nXF2 = st->nXF2;
     pf_tau = st->tau;
     e.ctl->booked = 0;
   }
+  // read before the first meeting (workgroup 0 writes them after the last)
+  const int v0 = e.ctl->vsel;
 
   // Sum of the group partials in group order; the Gram into both halves of G.
   {
     const int nent = kScalars + gram_blocks((n + 3) >> 2) * 16;
     constexpr int kChunk = 16;
-    for (int idx = tid; idx < nent; idx += kStepThreads) {
+    for (int idx = gtid; idx < nent; idx += teams * kStepThreads) {
       double sum = 0.0;
       for (int q0 = 0; q0 < d.groups; q0 += kChunk) {
         const int c = min(kChunk, d.groups - q0);
@@ -224,47 +319,60 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
         const int bj = packed_col(blk), bi = blk - bj * (bj + 1) / 2;
         const int i = 4 * bi + (el >> 2), j = 4 * bj + (el & 3);
         if (i <= j && j < n) {
-          e.G[i * nb + j] = sum;
-          e.G[j * nb + i] = sum;
+          st_to<TEAM>(as_global<double>(static_cast<void*>(e.G + i * nb + j)), sum);
+          st_to<TEAM>(as_global<double>(static_cast<void*>(e.G + j * nb + i)), sum);
         }
       }
     }
   }
   if (tid < 8) mx[tid >> 2][tid & 3] = 0u;
-  __syncthreads();
-  if (tid == 0) {
+  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if (tid == 0 && g == 0) {  // its scalars are this workgroup's own
     double t = 0.0;
     s_go = control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);
     s_tau = t;
+    if constexpr (TEAM) {
+      __hip_atomic_store(&e.ctl->tau, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&e.ctl->go, static_cast<uint32_t>(s_go), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
-  __syncthreads();
-  if (!s_go) return;
+  if constexpr (!TEAM) {
+    __syncthreads();
+    if (!s_go) return;
+  }
   STEP_MARK(0);
-  const double tau = s_tau;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), gw = g * kStepWaves + wv;
   const int l = tid & 63, lr = l >> 4, lc = l & 15, nt = nb >> 4;
   double* tb = tbuf[wv];
   const d4 zero = {0.0, 0.0, 0.0, 0.0};
-  auto put = [&](double* M) { return [M, nb](int bi, int bj, const d4& v) { store_block(M, nb, bi, bj, v); }; };
+  auto put = [&](double* M) { return [M, nb](int bi, int bj, const d4& v) { store_block<TEAM>(M, nb, bi, bj, v); }; };
   auto put_sym = [&](double* M) {
-    return [=](int bi, int bj, const d4& v) { store_mirrored(M, nb, bi, bj, v, zero, tb); };
+    return [=](int bi, int bj, const d4& v) { store_mirrored<TEAM>(M, nb, bi, bj, v, zero, tb); };
   };
 
   // W = G V (G symmetric), S = V^T W, C = V^T V (C: upper blocks only)
-  const int v0 = e.ctl->vsel;
   const double* V = e.v(v0);
-  int u = wv;
-  product<false>(u, e.G, V, nb, put(e.W));
-  __syncthreads();
-  u = wv;
-  product<true>(u, V, e.W, nb, put_sym(e.S));
-  product<true>(u, V, V, nb, put(e.C));
-  // V^T, for the products with V as the left factor (or V^T as the right one)
-  for (int t = wv; t < nt * nt; t += kStepWaves) {
-    const int bi = t / nt, bj = t - bi * nt;
-    store_block(e.VT[0], nb, bj, bi, transposed(load_block(V, nb, bi, bj), tb));
+  int u = gw;
+  product<TEAM, false>(u, nw, e.G, V, nb, put(e.W));
+  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if constexpr (TEAM) {
+    if (tid == 0) {
+      s_tau = __hip_atomic_load(&e.ctl->tau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_go = static_cast<int>(__hip_atomic_load(&e.ctl->go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    }
+    __syncthreads();
+    if (!s_go) return;
   }
-  __syncthreads();
+  const double tau = s_tau;
+  u = gw;
+  product<TEAM, true>(u, nw, V, e.W, nb, put_sym(e.S));
+  product<TEAM, true>(u, nw, V, V, nb, put(e.C));
+  // V^T, for the products with V as the left factor (or V^T as the right one)
+  for (int t = gw; t < nt * nt; t += nw) {
+    const int bi = t / nt, bj = t - bi * nt;
+    store_block<TEAM>(e.vt(0), nb, bj, bi, transposed(load_block<TEAM>(V, nb, bi, bj), tb));
+  }
+  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
 
   STEP_MARK(2);
   int s = 0;
@@ -272,7 +380,8 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   for (;; ++s) {
     unsigned* mp = mx[s & 1];
     if (tid < n) {
-      const double sii = e.S[tid * nb + tid], m = e.C[tid * nb + tid] - 1.0;
+      const double sii = ld<TEAM>(as_global<double>(static_cast<const void*>(e.S + tid * (nb + 1))));
+      const double m = ld<TEAM>(as_global<double>(static_cast<const void*>(e.C + tid * (nb + 1)))) - 1.0;
       const double di = fma(-m, sii, sii), si = sqrt_or_zero(di);
       const double wi = si > tau ? 1.0 - tau * rcp_pos(si) : 0.0;
       sd[tid] = sii;
@@ -282,9 +391,9 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     }
     __syncthreads();
     float mz = 0.0f, mk = 0.0f, mm = 0.0f, mt = 0.0f;
-    for (int t = wv; t < nt * (nt + 1) / 2; t += kStepWaves) {
+    for (int t = gw; t < nt * (nt + 1) / 2; t += nw) {
       const int bj = packed_col(t), bi = t - bj * (bj + 1) / 2;
-      const d4 cb = load_block(e.C, nb, bi, bj), sb = load_block(e.S, nb, bi, bj);
+      const d4 cb = load_block<TEAM>(e.C, nb, bi, bj), sb = load_block<TEAM>(e.S, nb, bi, bj);
       const int j = 16 * bj + lc;
       d4 z = zero, k = zero;
 #pragma unroll
@@ -306,13 +415,21 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
           mm = fmaxf(mm, fabsf(static_cast<float>(cb[r])));
         }
       }
-      store_mirrored(e.Z, nb, bi, bj, z, zero, tb);
-      store_mirrored(e.K, nb, bi, bj, zero, k, tb);
+      store_mirrored<TEAM>(e.Z, nb, bi, bj, z, zero, tb);
+      store_mirrored<TEAM>(e.K, nb, bi, bj, zero, k, tb);
     }
     wave_max_to(mz, &mp[0]);
     wave_max_to(mk, &mp[1]);
     wave_max_to(mm, &mp[2]);
     wave_max_to(mt, &mp[3]);
+    if constexpr (TEAM) {
+      __syncthreads();
+      unsigned* all = e.ctl->mx[s];
+      if (tid < 4 && mp[tid] != 0u)
+        __hip_atomic_fetch_max(&all[tid], mp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+      if (tid < 4) mp[tid] = __hip_atomic_load(&all[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     mz = __uint_as_float(mp[0]);
     mk = __uint_as_float(mp[1]);
@@ -327,7 +444,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     // U = I + K + T/2 - M/2, T = K^2 = -K^T K (to fourth order for large K)
     auto eye = [&](int bi, int bj) {  // I - M/2
       d4 h = zero;
-      const d4 c = load_block(e.C, nb, bi, bj);
+      const d4 c = load_block<TEAM>(e.C, nb, bi, bj);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double id = bi == bj && lr + 4 * r == lc ? 1.0 : 0.0;
@@ -335,55 +452,55 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       }
       return h;
     };
-    u = wv;
+    u = gw;
     if (!(mt > kWideFourth)) {
-      product<true>(u, e.K, e.K, nb, [&](int bi, int bj, const d4& v) {
-        store_mirrored(e.U, nb, bi, bj, eye(bi, bj) - 0.5 * v, load_block(e.K, nb, bi, bj), tb);
+      product<TEAM, true>(u, nw, e.K, e.K, nb, [&](int bi, int bj, const d4& v) {
+        store_mirrored<TEAM>(e.U, nb, bi, bj, eye(bi, bj) - 0.5 * v, load_block<TEAM>(e.K, nb, bi, bj), tb);
       });
     } else {
-      product<true>(u, e.K, e.K, nb,
-                    [&](int bi, int bj, const d4& v) { store_mirrored(e.T, nb, bi, bj, -v, zero, tb); });
-      __syncthreads();
+      product<TEAM, true>(u, nw, e.K, e.K, nb,
+                    [&](int bi, int bj, const d4& v) { store_mirrored<TEAM>(e.T, nb, bi, bj, -v, zero, tb); });
+      if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
       // K T = -K^T T into W, then T^2 and U (a block of both has one owner)
-      u = wv;
-      product<true>(u, e.K, e.T, nb, [&](int bi, int bj, const d4& v) { store_block(e.W, nb, bi, bj, -v); });
-      u = wv;
-      product<true>(u, e.T, e.T, nb, [&](int bi, int bj, const d4& v) {
-        const d4 h = eye(bi, bj) + 0.5 * load_block(e.T, nb, bi, bj) + v * (1.0 / 24.0);
-        const d4 k = load_block(e.K, nb, bi, bj) + load_block(e.W, nb, bi, bj) * (1.0 / 6.0);
-        store_mirrored(e.U, nb, bi, bj, h, k, tb);
+      u = gw;
+      product<TEAM, true>(u, nw, e.K, e.T, nb, [&](int bi, int bj, const d4& v) { store_block<TEAM>(e.W, nb, bi, bj, -v); });
+      u = gw;
+      product<TEAM, true>(u, nw, e.T, e.T, nb, [&](int bi, int bj, const d4& v) {
+        const d4 h = eye(bi, bj) + 0.5 * load_block<TEAM>(e.T, nb, bi, bj) + v * (1.0 / 24.0);
+        const d4 k = load_block<TEAM>(e.K, nb, bi, bj) + load_block<TEAM>(e.W, nb, bi, bj) * (1.0 / 6.0);
+        store_mirrored<TEAM>(e.U, nb, bi, bj, h, k, tb);
       });
     }
-    __syncthreads();
+    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
     // W = S U, V' = V U (and its transpose);  S = U^T W, C = V'^T V'
     double* Vn = e.v(WideEig::vsel(v0, s + 1));
-    u = wv;
-    product<false>(u, e.S, e.U, nb, put(e.W));
-    product<false>(u, e.VT[s & 1], e.U, nb, [&](int bi, int bj, const d4& v) {
-      store_block(Vn, nb, bi, bj, v);
-      store_block(e.VT[~s & 1], nb, bj, bi, transposed(v, tb));
+    u = gw;
+    product<TEAM, false>(u, nw, e.S, e.U, nb, put(e.W));
+    product<TEAM, false>(u, nw, e.vt(s & 1), e.U, nb, [&](int bi, int bj, const d4& v) {
+      store_block<TEAM>(Vn, nb, bi, bj, v);
+      store_block<TEAM>(e.vt((s + 1) & 1), nb, bj, bi, transposed(v, tb));
     });
     V = Vn;
-    __syncthreads();
-    u = wv;
-    product<true>(u, e.U, e.W, nb, put_sym(e.S));
-    product<true>(u, V, V, nb, put(e.C));
-    __syncthreads();
+    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+    u = gw;
+    product<TEAM, true>(u, nw, e.U, e.W, nb, put_sym(e.S));
+    product<TEAM, true>(u, nw, V, V, nb, put(e.C));
+    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
     STEP_MARK(2);
   }
   if (!ok) return;  // the Jacobi kernel takes over, from V at v0
 
   // P = V (Z V^T) (exactly symmetric)
-  const double* Vt = e.VT[s & 1];
-  u = wv;
-  product<false>(u, e.Z, Vt, nb, put(e.W));
-  __syncthreads();
-  u = wv;
-  product<true>(u, Vt, e.W, nb, [&](int bi, int bj, const d4& v) {
-    store_mirrored(static_cast<T*>(d.P), nb, bi, bj, v, zero, tb);
+  const double* Vt = e.vt(s & 1);
+  u = gw;
+  product<TEAM, false>(u, nw, e.Z, Vt, nb, put(e.W));
+  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  u = gw;
+  product<TEAM, true>(u, nw, Vt, e.W, nb, [&](int bi, int bj, const d4& v) {
+    store_mirrored<false>(static_cast<T*>(d.P), nb, bi, bj, v, zero, tb);
   });
   const int rank = __syncthreads_count(tid < n && w[tid] != 0.0);
-  if (tid == 0) {
+  if (tid == 0 && g == 0) {
     e.ctl->vsel = WideEig::vsel(v0, s);
     e.ctl->booked = kd + 1;
     st->rank = rank;
@@ -399,13 +516,28 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
 
 }  // namespace
 
-hipError_t launch_eig_steps(int dtype, int grid, hipStream_t stream, const SolveDesc* descs,
+// One wave per block of the widest phase (W and V', 2 (nb/16)^2 blocks), as long
+// as the launch stays within kTeamGroups workgroups: with at most four launches
+// at a time on the device's queues, every workgroup of every team is running or
+// will be, whatever order they are placed in.
+constexpr int kTeamGroups = 64;
+int steps_team(int nb, int grid) {
+  const int nt = nb / 16, most = (2 * nt * nt + kStepWaves - 1) / kStepWaves;
+  return std::max(1, std::min(most, kTeamGroups / std::max(grid, 1)));
+}
+
+hipError_t launch_eig_steps(int dtype, int grid, int team, hipStream_t stream, const SolveDesc* descs,
                             const int32_t* ids) {
   if (grid <= 0) return hipSuccess;
-  if (dtype == 1)
-    RPCA_LAUNCH(k_eig_steps<float>, dim3(grid), dim3(kStepThreads), 0, stream, descs, ids);
+  const dim3 g(team, grid), b(kStepThreads);
+  if (dtype == 1 && team > 1)
+    RPCA_LAUNCH((k_eig_steps<float, true>), g, b, 0, stream, descs, ids);
+  else if (dtype == 1)
+    RPCA_LAUNCH((k_eig_steps<float, false>), g, b, 0, stream, descs, ids);
+  else if (team > 1)
+    RPCA_LAUNCH((k_eig_steps<double, true>), g, b, 0, stream, descs, ids);
   else
-    RPCA_LAUNCH(k_eig_steps<double>, dim3(grid), dim3(kStepThreads), 0, stream, descs, ids);
+    RPCA_LAUNCH((k_eig_steps<double, false>), g, b, 0, stream, descs, ids);
   return hipGetLastError();
 }
 

@@ -105,6 +105,11 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   const int nb = d.nb;
   const int kd = st->iter;
   const WideEig we(d);
+  if (tid == 0) {  // for the steps' next launch
+    we.ctl->arrived = 0u;
+    we.ctl->lost = 0u;
+  }
+  if (tid < (kWideSteps + 1) * 4) we.ctl->mx[tid >> 2][tid & 3] = 0u;
   if (kd == 0) {
     // the steps' matrices are zero outside n x n, and V is in its first buffer
     const int len = kWideMats * nb * nb;

@@ -608,8 +608,8 @@ static hipError_t enqueue_iterations_at(const Plan& plan, const Lanes& L, int it
         ev_begin(s, 1, first_iter + k, static_cast<int>(l), -1);
         const LaunchEvents ev = t_launch_events;  // timed as one: first launch to last
         t_launch_events = LaunchEvents{ev.start, nullptr};
-        EQ(launch_eig_steps(plan.dtype == RPCA_F32 ? 1 : 0, lr.wide_cnt, s, plan.descs,
-                            plan.ids + lr.wide_off));
+        EQ(launch_eig_steps(plan.dtype == RPCA_F32 ? 1 : 0, lr.wide_cnt, steps_team(lr.nb_max, lr.wide_cnt), s,
+                            plan.descs, plan.ids + lr.wide_off));
         t_launch_events = LaunchEvents{};
         int left = lr.wide_cnt;
         for (const auto& er : lr.eigs) {

@@ -60,8 +60,9 @@ int eig_class(int n);
 hipError_t launch_eig_wide(int dtype, int ncls, int grid, hipStream_t stream,
                            const SolveDesc* descs, const int32_t* ids);
 // Warm-started steps of the same solves, launched before launch_eig_wide
-// (which returns at once where they converged).
-hipError_t launch_eig_steps(int dtype, int grid, hipStream_t stream, const SolveDesc* descs,
+// (which returns at once where they converged).  `team` workgroups per solve.
+int steps_team(int nb, int grid);
+hipError_t launch_eig_steps(int dtype, int grid, int team, hipStream_t stream, const SolveDesc* descs,
                             const int32_t* ids);
 // MFMA streaming kernel.  FP32 storage: nb a multiple of 16 up to 144;
 // prec 0 = FP32 rebuild / FP64 Gram, 1 = split-BF16 (3 products) for both,
