@@ -115,8 +115,17 @@ __device__ inline void split_any(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
   }
 }
 
+// Wavefronts per SIMD that the registers are held to: two workgroups per CU
+// where that needs no spills, so that one's loads and barriers are hidden
+// behind the other's products.  (FP32 at 64 frames fits too, with L over the A
+// tile, but without its next tile's loads in flight: 3 to 7% slower.)
+template <typename T>
+__host__ __device__ constexpr int waves_per_simd(int nb, int prec) {
+  return sizeof(T) == 4 && nb <= 48 ? 4 : 2;
+}
+
 template <typename T, int NB, int PHASE, int PREC>
-__global__ void __launch_bounds__(waves_for(NB) * 64)
+__global__ void __launch_bounds__(waves_for(NB) * 64, waves_per_simd<T>(NB, PREC))
 k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) {
   static_assert(NB % 16 == 0 && NB <= 144, "frame class");
   constexpr bool F64 = std::is_same<T, double>::value;
@@ -127,6 +136,7 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
   constexpr int NK4 = NB / 4;                           // f32 k-steps of the rebuild
   constexpr int NT16 = NB / 16;                         // 16-frame blocks
   constexpr bool X6 = PREC == 2;
+  constexpr bool TIGHT = NB <= 64;
   constexpr int NBK = PREC ? (NB + 31) / 32 * 32 : NB;  // contraction length of the rebuild
   constexpr int NKB = NBK / 32;                         // bf16 k-steps of the rebuild
   constexpr int NGT = NT16 * (NT16 + 1) / 2;            // Gram output blocks (upper)
@@ -147,7 +157,9 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
   __shared__ T Ps[PL ? NB * LDP : 1];
 
   const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
+  // the wave's number in a scalar register: frame offsets are then scalar too,
+  // and a load or store is one scalar base plus the lane
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const WorkItem wi = items[blockIdx.x];
   const SolveDesc& d = descs[wi.solve];
   SolveState* st = d.st;
@@ -256,10 +268,10 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
         for (int q = 0; q < NQ; ++q) {
           const int j = w + NW * q;
           if (j >= n) continue;
-          const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(p);
-          as_global<T>(d.Lout)[off] = T(0);
-          as_global<T>(d.Sout)[off] = T(0);
-          if (d.Yout) as_global<T>(d.Yout)[off] = T(0);
+          const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(tile) * R;
+          (as_global<T>(d.Lout) + off)[l] = T(0);
+          (as_global<T>(d.Sout) + off)[l] = T(0);
+          if (d.Yout) (as_global<T>(d.Yout) + off)[l] = T(0);
         }
       }
       return;
@@ -270,25 +282,44 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
   const bool read_sy = REB && k >= 1 && !first;
   const gptr<const T> S0 = as_global<T>(d.S0);
   const gptr<const T> Y0 = as_global<T>(d.Y0);
-  auto load_tile = [&](int tile, T* xr, T* sr, T* yr) {
-    const int64_t p = static_cast<int64_t>(tile) * R + l;
+  // Lanes past the last row and waves past the last frame load the last one's
+  // entries again (never used): no load is under a lane mask or a branch, so
+  // none is waited for where that ends, and the bases are scalar.  This took
+  // the FP64 classes of 112 and 128 frames from 412 and 604 bytes of spilled
+  // registers per lane to 52 and 192 (whole iterations of 96133 x 97 and x 128:
+  // 510 and 695 us before, 425 and 553 now) and lets two workgroups of the
+  // 48-frame class share a CU with three BF16 planes (1048576 x 40: 345 and 278
+  // us).  The FP32 classes gain 0 to 5%.
+  const size_t first_off = static_cast<size_t>(w) * static_cast<size_t>(m);
+  const size_t step_off = static_cast<size_t>(NW) * static_cast<size_t>(m);
+  auto load_tile = [&](int tile, auto q0, auto q1, T* xr, T* sr, T* yr) {  // frames q0 <= q < q1
+    const int64_t p0 = static_cast<int64_t>(tile) * R;
+    const unsigned lane = static_cast<unsigned>(min(static_cast<int64_t>(l), m - 1 - p0));
+    auto from = [&](gptr<const T> M, T* v) {
+      gptr<const T> col =
+          M + (static_cast<size_t>(min(w + NW * q0(), n - 1)) * static_cast<size_t>(m) + static_cast<size_t>(p0));
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int j = w + NW * q;
-      xr[q] = T(0);
-      sr[q] = T(0);
-      yr[q] = T(0);
-      if (j < n && p < m) {
-        const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(p);
-        xr[q] = X[off];
-        if constexpr (WARM) {
-          if (d.S0) sr[q] = S0[off];
-          if (d.Y0) yr[q] = Y0[off];
-        } else if (read_sy) {
-          sr[q] = Sin[off];
-          yr[q] = Yin[off];
-        }
+      for (int q = q0(); q < q1(); ++q) {
+        if (q > q0()) col += step_off & -static_cast<size_t>(w + NW * q < n);  // no branch
+        v[q] = col[lane];
       }
+    };
+    auto none = [&](T* v) {
+#pragma unroll
+      for (int q = q0(); q < q1(); ++q) v[q] = T(0);
+    };
+    from(X, xr);
+    if constexpr (WARM) {
+      if (d.S0) from(S0, sr);
+      else none(sr);
+      if (d.Y0) from(Y0, yr);
+      else none(yr);
+    } else if (read_sy) {
+      from(Sin, sr);
+      from(Yin, yr);
+    } else {
+      none(sr);
+      none(yr);
     }
   };
   // With few frames per thread the next tile's loads are issued before the
@@ -296,14 +327,40 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
   // bytes of each of X, S, Y per thread).
   constexpr bool PF = NQ * static_cast<int>(sizeof(T)) <= 40;
   T xn[PF ? NQ : 1], sn_[PF ? NQ : 1], yn[PF ? NQ : 1];
+  using Q0 = std::integral_constant<int, 0>;
+  using QN = std::integral_constant<int, NQ>;
   if constexpr (PF) {
-    if (t0 < t1) load_tile(t0, xn, sn_, yn);
+    if (t0 < t1) load_tile(t0, Q0{}, QN{}, xn, sn_, yn);
   }
   for (int tile = t0; tile < t1; ++tile) {
     const int64_t p = static_cast<int64_t>(tile) * R + l;
     const bool valid = p < m;
     T x[NQ], y[NQ], sv[NQ];
     // 1. load, A tile
+    auto a_tile = [&](auto q0, auto q1) {
+#pragma unroll
+      for (int q = q0(); q < q1(); ++q) {
+        const int j = w + NW * q;
+        T a = T(0);
+        if (j < n && valid) {
+          if constexpr (INIT) {
+            const double xd = static_cast<double>(x[q]);
+            s1 += fabs(xd);
+            s2 = fma(xd, xd, s2);
+            nf += __builtin_isfinite(x[q]) ? 0.0 : 1.0;
+            a = x[q];
+          } else {
+            a = fma(y[q], imu, x[q] - sv[q]);
+            if constexpr (WARM) {  // the buffers the first update pass reads
+              const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(tile) * R;
+              (as_global<T>(d.S[0]) + off)[l] = sv[q];
+              (as_global<T>(d.Y[0]) + off)[l] = y[q];
+            }
+          }
+        }
+        At[j * LDA + l] = a;
+      }
+    };
     if constexpr (PF) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
@@ -311,33 +368,17 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
         sv[q] = sn_[q];
         y[q] = yn[q];
       }
+      a_tile(Q0{}, QN{});
+      if (tile + 1 < t1) load_tile(tile + 1, Q0{}, QN{}, xn, sn_, yn);
+    } else if constexpr (F64 && NB >= 80) {  // in two halves: half the registers for S
+      using QH = std::integral_constant<int, (NQ + 1) / 2>;
+      load_tile(tile, Q0{}, QH{}, x, sv, y);
+      a_tile(Q0{}, QH{});
+      load_tile(tile, QH{}, QN{}, x, sv, y);
+      a_tile(QH{}, QN{});
     } else {
-      load_tile(tile, x, sv, y);
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int j = w + NW * q;
-      T a = T(0);
-      if (j < n && valid) {
-        if constexpr (INIT) {
-          const double xd = static_cast<double>(x[q]);
-          s1 += fabs(xd);
-          s2 = fma(xd, xd, s2);
-          nf += __builtin_isfinite(x[q]) ? 0.0 : 1.0;
-          a = x[q];
-        } else {
-          a = fma(y[q], imu, x[q] - sv[q]);
-          if constexpr (WARM) {  // the buffers the first update pass reads
-            const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(p);
-            as_global<T>(d.S[0])[off] = sv[q];
-            as_global<T>(d.Y[0])[off] = y[q];
-          }
-        }
-      }
-      At[j * LDA + l] = a;
-    }
-    if constexpr (PF) {
-      if (tile + 1 < t1) load_tile(tile + 1, xn, sn_, yn);
+      load_tile(tile, Q0{}, QN{}, x, sv, y);
+      a_tile(Q0{}, QN{});
     }
     __syncthreads();
 
@@ -356,13 +397,26 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
           const bool act = owns[0] && rb < R / 16;
           d4 acc = {0.0, 0.0, 0.0, 0.0};
           if (act) {
+            constexpr int KG = 4, NG = NK4 / KG;
+            double a[2][KG], b[2][KG];
+            auto read = [&](int g) {
 #pragma unroll
-            for (int kk = 0; kk < NK4; ++kk) {
-              const double b = At[(4 * kk + (l >> 4)) * LDA + 16 * rb + (l & 15)];
-              double a;
-              if constexpr (PL) a = Ps[(16 * t + (l & 15)) * LDP + 4 * kk + (l >> 4)];
-              else a = pa[0][kk];
-              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+              for (int k = 0; k < KG; ++k) {
+                const int kk = KG * g + k;
+                b[g & 1][k] = At[(4 * kk + (l >> 4)) * LDA + 16 * rb + (l & 15)];
+                if constexpr (PL) a[g & 1][k] = Ps[(16 * t + (l & 15)) * LDP + 4 * kk + (l >> 4)];
+                else a[g & 1][k] = pa[0][kk];
+              }
+            };
+            read(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+              if (g + 1 < NG) read(g + 1);
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int k = 0; k < KG; ++k)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[g & 1][k], b[g & 1][k], acc, 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
             }
           }
           __syncthreads();  // every wave is past its reads of this step's rows
@@ -392,6 +446,7 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
               } else {
 #pragma unroll
                 for (int kk = 0; kk < NKB; ++kk) {
+                  if (TIGHT) __builtin_amdgcn_sched_barrier(0);
                   bf8 bh, bm, bl;
 #pragma unroll
                   for (int e = 0; e < 8; ++e) {
@@ -416,20 +471,21 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
 
       // 3. elementwise step (or the final L); FP64 reads L and writes the
       // next A at the same place of the A tile (the thread's own entries)
+      size_t off = first_off + static_cast<size_t>(tile) * R;  // frame w's, then NW frames further
+      asm volatile("" : "+s"(off));  // not NQ offsets kept in registers
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
+      for (int q = 0; q < NQ; ++q, off += step_off) {
         const int j = w + NW * q;
         T lv;
         if constexpr (F64) lv = At[j * LDA + l];
         else lv = Lt[j * LDA + l];
         T apj = T(0);
         if (j < n && valid) {
-          const size_t off = static_cast<size_t>(j) * static_cast<size_t>(m) + static_cast<size_t>(p);
           if constexpr (FIN) {
-            as_global<T>(d.Lout)[off] = lv;
-            as_global<T>(d.Sout)[off] = as_global<T>(static_cast<const void*>(d.S[k & 1]))[off];
+            (as_global<T>(d.Lout) + off)[l] = lv;
+            (as_global<T>(d.Sout) + off)[l] = (as_global<T>(static_cast<const void*>(d.S[k & 1])) + off)[l];
             if (d.Yout)
-              as_global<T>(d.Yout)[off] = as_global<T>(static_cast<const void*>(d.Y[k & 1]))[off];
+              (as_global<T>(d.Yout) + off)[l] = (as_global<T>(static_cast<const void*>(d.Y[k & 1])) + off)[l];
           } else {
             const T tt = fma(y[q], imu, x[q]) - lv;                 // X - L + Y/mu
             const T sn = tt - clamp_t(tt, gam);                     // Eq. 5 shrink
@@ -438,8 +494,8 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
             const double zd = static_cast<double>(z);
             r2 = fma(zd, zd, r2);
             apj = fma(yn, imu, x[q] - sn);                          // next X - S + Y/mu
-            Sout[off] = sn;
-            Yout[off] = yn;
+            (Sout + off)[l] = sn;
+            (Yout + off)[l] = yn;
           }
         }
         if constexpr (!FIN) At[j * LDA + l] = apj;
@@ -465,6 +521,7 @@ k_wide(const SolveDesc* __restrict__ descs, const WorkItem* __restrict__ items) 
             f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < R / 32; ++kk) {
+              if (TIGHT) __builtin_amdgcn_sched_barrier(0);
               bf8 ah, am, al, bh, bm, bl;
 #pragma unroll
               for (int e = 0; e < 8; ++e) {
