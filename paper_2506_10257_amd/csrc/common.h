@@ -130,6 +130,7 @@ struct WideCtl {
   uint32_t arrived;                  // meetings, counted by workgroup
   uint32_t lost;                     // a workgroup gave up waiting
   uint32_t go;                       // the control step's answer
+  uint32_t ready;                    // the first eigensolve's V and threshold are there
   uint32_t mx[kWideSteps + 1][4];    // maxima over a step's pairs
   double tau;
 };

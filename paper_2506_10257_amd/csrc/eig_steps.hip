@@ -22,6 +22,7 @@
 // 2018), so it converges with E.  Where the steps do not converge (strongly
 // rotated dense clusters, or more than kWideSteps steps) the Jacobi kernel
 // (eig_wide.hip), launched next, runs sweeps from the previous iteration's V.
+// It also runs the first sweeps of a solve's first eigensolve.
 //
 // Bound: with one workgroup, by its CU's matrix cores: a product is 2 nb^3 FP64
 // operations (307 GFLOP/s: 19 us at 144 frames, 9 us at 112), a launch has about
@@ -264,8 +265,8 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const int tid = threadIdx.x;
   const SolveDesc& d = descs[ids[blockIdx.y]];
   SolveState* st = d.st;
-  // a solve's first eigensolve is the Jacobi kernel's
-  if (st->done || st->iter == 0) return;
+  // a solve's first eigensolve begins with the Jacobi kernel's sweeps
+  if (st->done || (st->iter == 0 && WideEig(d).ctl->ready == 0u)) return;
 #ifdef RPCA_TRACE
   int64_t tprev = RPCA_NOW();
 #define STEP_MARK(i)                              \
@@ -328,8 +329,8 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   if (tid < 8) mx[tid >> 2][tid & 3] = 0u;
   if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
   if (tid == 0 && g == 0) {  // its scalars are this workgroup's own
-    double t = 0.0;
-    s_go = control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);
+    double t = pf_tau;
+    s_go = kd == 0 ? 1 : control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);  // kd = 0: done there
     s_tau = t;
     if constexpr (TEAM) {
       __hip_atomic_store(&e.ctl->tau, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -517,10 +518,13 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
 }  // namespace
 
 // One wave per block of the widest phase (W and V', 2 (nb/16)^2 blocks), as long
-// as the launch stays within kTeamGroups workgroups: with at most four launches
-// at a time on the device's queues, every workgroup of every team is running or
-// will be, whatever order they are placed in.
-constexpr int kTeamGroups = 64;
+// as the launch stays within kTeamGroups workgroups: a CU holds one of them, so
+// the launches of six streams at once (the server's) are all resident or will
+// be, whatever order their workgroups are placed in.  Fewer workgroups per
+// solve are slower in step (100 frames, small images, us per iteration: 205 for
+// one solve, 275 for 6, 342 for 16, 511 for 32 on four streams), one per solve
+// is the least.
+constexpr int kTeamGroups = 42;
 int steps_team(int nb, int grid) {
   const int nt = nb / 16, most = (2 * nt * nt + kStepWaves - 1) / kStepWaves;
   return std::max(1, std::min(most, kTeamGroups / std::max(grid, 1)));

@@ -28,14 +28,15 @@
 //   * a round is [apply the round's rotations] barrier [the first wave
 //     computes the next round's rotations from the updated G] barrier.
 //
-// From a solve's second eigensolve on, the simultaneous steps of eig_steps.hip
-// run first; where they converge, this kernel returns at once.  Where they do
-// not, it starts from the previous iteration's eigenvectors V, brought
-// back to orthogonality by one Newton-Schulz step V <- V (3I - V^T V) / 2, on
-// G~ = V^T G V.  The products run on the f64 matrix cores (W = G V goes through
-// a per-solve global scratch buffer, since LDS holds G and V already).  With V
-// in global memory the projector P = V diag(w) V^T is also formed on the f64
-// matrix cores.
+// The simultaneous steps of eig_steps.hip do most of the work.  A solve's first
+// eigensolve starts here, from V = I (`start`): after two sweeps or more, once
+// the rotations are small, V is left to the steps.  From then on the steps run
+// first, and where they converge this kernel returns at once.  Where they do
+// not, it starts from the previous V, brought back to orthogonality by one
+// Newton-Schulz step V <- V (3I - V^T V) / 2, on G~ = V^T G V.  The products run
+// on the f64 matrix cores (W = G V goes through a per-solve global scratch
+// buffer, since LDS holds G and V already).  With V in global memory the
+// projector P = V diag(w) V^T is also formed on the f64 matrix cores.
 #include <type_traits>
 
 #include "common.h"
@@ -51,6 +52,13 @@ using namespace eigk;
 // their rotations as an FP32 increment in LDS (74.5 KB beside packed G).
 constexpr int kEigIncMaxN = 136;
 
+// Row sum of tangents at which a first eigensolve goes over to the steps.  A
+// sweep takes 230 (500) us at 100 (132) frames, a step about 30; whole solves of
+// 40 iterations, sweeps to the end / 0.9, and no tangent above 0.25 / 2: 14.64 /
+// 14.55 / 13.96 ms at 512 x 512 x 100, 24.69 / 24.22 / 22.38 at 132, and 10.03 /
+// 9.61 / 9.35 for 20 iterations of 251 x 383 x 97 FP64.
+constexpr float kStartRowSum = 2.0f;
+
 __device__ inline int pk(int i, int j) {  // packed upper index, i <= j
   return j * (j + 1) / 2 + i;
 }
@@ -58,7 +66,7 @@ __device__ inline int pks(int i, int j) { return i <= j ? pk(i, j) : pk(j, i); }
 
 template <typename T, int NMAX, int NT>
 __global__ void __launch_bounds__(NT)
-k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
+k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids, int start) {
   constexpr bool VG = NMAX > kEigWideMaxN;  // V in global memory
   // FP32 solves of up to kEigIncMaxN frames in the device-memory class keep
   // V fixed during the sweeps and accumulate the sweeps' rotations as an
@@ -79,6 +87,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   __shared__ double tdt[NPM];
   __shared__ double w[NMAX];
   __shared__ double scal[kScalars];
+  __shared__ unsigned rsum[NMAX];
   __shared__ int s_go;
   __shared__ double s_tau;
 
@@ -110,15 +119,18 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     we.ctl->lost = 0u;
   }
   if (tid < (kWideSteps + 1) * 4) we.ctl->mx[tid >> 2][tid & 3] = 0u;
-  if (kd == 0) {
+  // a solve's first eigensolve that the steps did not finish: as a later one
+  const bool handed = kd == 0 && !start && we.ctl->ready != 0u;
+  if (kd == 0 && !handed) {
     // the steps' matrices are zero outside n x n, and V is in its first buffer
     const int len = kWideMats * nb * nb;
     for (int idx = tid; idx < len; idx += NT) we.G[idx] = 0.0;
     if (tid == 0) {
       we.ctl->booked = 0;
       we.ctl->vsel = 0;
+      we.ctl->ready = 0u;
     }
-  } else if (we.ctl->booked == kd) {
+  } else if (kd > 0 && we.ctl->booked == kd) {
     return;  // the steps (eig_steps.hip) wrote this iteration's P
   }
   double* const dV = kd == 0 ? d.V : we.v(we.ctl->vsel);
@@ -129,7 +141,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     pf_tau = st->tau;
   }
 
-  const bool warm = kd > 0;
+  const bool warm = kd > 0 || handed;
   // (warm starts only: the cold start's rotations build all of V, and D
   // would be of order one)
   const bool vinc = VI && warm && n <= kEigIncMaxN;
@@ -191,8 +203,8 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   __syncthreads();
 
   if (tid == 0) {
-    double t = 0.0;
-    s_go = control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);
+    double t = pf_tau;
+    s_go = handed ? 1 : control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);
     s_tau = t;
   }
   __syncthreads();
@@ -360,6 +372,36 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     }
   };
 
+  // Whether the steps are worth trying from here: every row's sum of (clipped)
+  // tangents below kStartRowSum, in whole units, so that the order of the sum
+  // does not matter.  Where they then fail, the sweeps go on from this V.
+  auto small_rotations = [&] {
+    constexpr float kUnit = 1048576.0f;  // 144 tangents of 0.5 fit 32 bits
+    if (tid < n) {
+      w[tid] = sqrt_or_zero(Gp[pk(tid, tid)]);
+      rsum[tid] = 0u;
+    }
+    __syncthreads();
+    int large = 0;
+    for (int idx = tid; idx < n * (n + 1) / 2; idx += NT) {
+      const int j = packed_col(idx), i = idx - j * (j + 1) / 2;
+      if (i == j) continue;
+      const double si = w[i], sj = w[j];
+      const double wi = si > tau ? 1.0 - tau * rcp_pos(si) : 0.0, wj = sj > tau ? 1.0 - tau * rcp_pos(sj) : 0.0;
+      const PairTerms pt = pair_terms<T>(Gp[idx], Gp[pk(i, i)], Gp[pk(j, j)], si, sj, wi, wj, tau, n);
+      const float t = fabsf(static_cast<float>(pt.t));
+      if (!(t <= static_cast<float>(kTangentMax))) large = 1;  // NaN
+      const unsigned u = static_cast<unsigned>(t * kUnit);
+      if (u != 0u) {
+        atomicAdd(&rsum[i], u);
+        atomicAdd(&rsum[j], u);
+      }
+    }
+    __syncthreads();
+    if (tid < n && static_cast<float>(rsum[tid]) >= kStartRowSum * kUnit) large = 1;
+    return __syncthreads_or(large) == 0;
+  };
+
   int sweeps = 0;
   for (; sweeps < kMaxSweeps && n > 1; ++sweeps) {
     int need = 0;
@@ -371,6 +413,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
     }
     make_round(0);
     if (!__syncthreads_or(need)) break;
+    if (start && sweeps >= 2 && small_rotations()) break;
     for (int r = 0; r < M; ++r) {
       // apply round r: G blocks and V items, in place.  The items of a
       // thread are disjoint from each other (and from every other thread's),
@@ -510,6 +553,19 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
   }
 
   EIG_MARK(2);
+  if (start) {  // the steps go on from V
+    if constexpr (!VG) {
+      for (int idx = tid; idx < nb * nb; idx += NT) {
+        const int i = idx / nb, j = idx - (idx / nb) * nb;
+        dV[idx] = (i < n && j < n) ? Vs[i * LDV + j] : 0.0;
+      }
+    }
+    if (tid == 0) {
+      we.ctl->ready = 1u;
+      st->sweeps_total += sweeps;
+    }
+    return;
+  }
   if (vinc && sweeps > 0) {
     // V <- V + V D on the f64 matrix cores; each wave keeps its 16 x 16
     // blocks in registers until every wave has read V, then adds them to its
@@ -624,20 +680,20 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids)
 
 }  // namespace
 
-hipError_t launch_eig_wide(int dtype, int ncls, int grid, hipStream_t stream, const SolveDesc* descs,
-                           const int32_t* ids) {
+hipError_t launch_eig_wide(int dtype, int ncls, int grid, bool start, hipStream_t stream,
+                           const SolveDesc* descs, const int32_t* ids) {
   if (grid <= 0) return hipSuccess;
   const dim3 g(grid), b(kEigWideThreads);
   if (ncls == kEigWideMaxN) {
     if (dtype == 1)
-      RPCA_LAUNCH((k_eig_wide<float, kEigWideMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids);
+      RPCA_LAUNCH((k_eig_wide<float, kEigWideMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids, start ? 1 : 0);
     else
-      RPCA_LAUNCH((k_eig_wide<double, kEigWideMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids);
+      RPCA_LAUNCH((k_eig_wide<double, kEigWideMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids, start ? 1 : 0);
   } else if (ncls == kEigHugeMaxN) {
     if (dtype == 1)
-      RPCA_LAUNCH((k_eig_wide<float, kEigHugeMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids);
+      RPCA_LAUNCH((k_eig_wide<float, kEigHugeMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids, start ? 1 : 0);
     else
-      RPCA_LAUNCH((k_eig_wide<double, kEigHugeMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids);
+      RPCA_LAUNCH((k_eig_wide<double, kEigHugeMaxN, kEigWideThreads>), g, b, 0, stream, descs, ids, start ? 1 : 0);
   } else {
     return hipErrorInvalidValue;
   }

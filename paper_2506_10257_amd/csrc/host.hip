@@ -581,7 +581,7 @@ hipError_t enqueue_init(const Plan& plan, const Lanes& L) {
     // solves with a given start: fix mu, then the Gram of A_1 = X - S0 + Y0/mu
     for (const auto& er : lr.warm_eigs) {
       if (er.first > kEigMaxN)
-        EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s,
+        EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, true, s,
                            plan.descs, plan.ids + er.second.first));
       else
         EQ(launch_eig(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s, plan.descs,
@@ -593,6 +593,10 @@ hipError_t enqueue_init(const Plan& plan, const Lanes& L) {
     if (lr.warm_gitem_cnt > 0)
       EQ(launch_reduce(lr.warm_gitem_cnt, reduce_chunks(lr.nb_max), s, plan.descs,
                        plan.gitems + lr.warm_gitem_off));
+    for (const auto& er : lr.eigs)
+      if (er.first > kEigMaxN)
+        EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, true, s,
+                           plan.descs, plan.ids + er.second.first));
   }
   return hipSuccess;
 }
@@ -616,8 +620,8 @@ static hipError_t enqueue_iterations_at(const Plan& plan, const Lanes& L, int it
           if (er.first <= kEigMaxN) continue;
           left -= er.second.second;
           if (left == 0) t_launch_events = LaunchEvents{nullptr, ev.stop};
-          EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, s, plan.descs,
-                             plan.ids + er.second.first));
+          EQ(launch_eig_wide(plan.dtype == RPCA_F32 ? 1 : 0, er.first, er.second.second, false, s,
+                             plan.descs, plan.ids + er.second.first));
         }
         ev_end(s);
       }

@@ -56,8 +56,10 @@ hipError_t launch_reset_states(int count, hipStream_t stream, const SolveDesc* d
 // Returns 16, 32, 64, kEigWideMaxN or kEigHugeMaxN (0 if n is too large).
 int eig_class(int n);
 // Classes above 64 frames: the in-place eigensolver, ncls = kEigWideMaxN
-// (V in LDS) or kEigHugeMaxN (V in global memory).
-hipError_t launch_eig_wide(int dtype, int ncls, int grid, hipStream_t stream,
+// (V in LDS) or kEigHugeMaxN (V in global memory).  start: the solves' control
+// step and the first sweeps of their first eigensolve, which the next
+// launch_eig_steps goes on with.
+hipError_t launch_eig_wide(int dtype, int ncls, int grid, bool start, hipStream_t stream,
                            const SolveDesc* descs, const int32_t* ids);
 // Warm-started steps of the same solves, launched before launch_eig_wide
 // (which returns at once where they converged).  `team` workgroups per solve.
