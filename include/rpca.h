@@ -165,8 +165,9 @@ int rpca_solve_ex(rpca_problem* prob, int32_t dtype, int32_t gram_mode, void* st
  * or rpca_solve_f64 (RPCA_F64), with the same arguments, defaults, status
  * codes and bitwise the same L, S and iteration count, but its workspace
  * lives in a static device array of the library, RPCA_NOALLOC_MAX_BYTES
- * (192 MiB) per device, reserved when the library's code is loaded on that
- * device and held until the process ends.  The call allocates no device
+ * (192 MiB) per device, and 2 MB more for the eigensolver of windows above 64
+ * frames, reserved when the library's code is loaded on that device and held
+ * until the process ends.  The call allocates no device
  * memory, no pinned host memory, no stream, event or graph: it launches on
  * `stream` directly and reads the solve state back between chunks of
  * iterations.

@@ -140,5 +140,15 @@ inline size_t wide_scratch_doubles(int n, int nb) {
   const size_t c = static_cast<size_t>(wide_class(n));
   return c * c + kWideCtlDoubles + static_cast<size_t>(kWideMats) * nb * nb;
 }
+// What of it the simultaneous steps take (bytes, in a layout of 256-byte
+// pieces), and the most for any window.
+inline size_t steps_bytes(int n, int nb) {
+  if (n <= kEigMaxN) return 0;
+  const size_t c = static_cast<size_t>(wide_class(n)), round = 255;
+  const size_t all = (wide_scratch_doubles(n, nb) * sizeof(double) + round) & ~round;
+  return all - ((c * c * sizeof(double) + round) & ~round);
+}
+constexpr size_t kStepsBytesMax =
+    (kWideCtlDoubles + static_cast<size_t>(kWideMats) * kEigHugeMaxN * kEigHugeMaxN) * sizeof(double) + 256;
 
 }  // namespace rpca

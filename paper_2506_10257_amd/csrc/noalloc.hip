@@ -32,7 +32,9 @@
 namespace rpca {
 namespace {
 
-static __device__ __align__(256) unsigned char scratch[RPCA_NOALLOC_MAX_BYTES];
+// The limit is on the workspace without the matrices of the eigensolver's steps
+// (windows above 64 frames, up to 2 MB), which have room of their own.
+static __device__ __align__(256) unsigned char scratch[RPCA_NOALLOC_MAX_BYTES + kStepsBytesMax];
 
 constexpr int kMaxDevices = 64;
 constexpr int kChunkFirst = 8;   // iterations between state reads, doubling ...
@@ -85,12 +87,13 @@ int solve_noalloc(const rpca_problem& p, int dtype, hipStream_t stream, int32_t*
   rec.mem = nullptr;  // the descriptors are written once the address is known
   const size_t ws = al256(rec.big.total);
   const size_t ctrl_bytes = plan_prepare(plan, recs, 1, dtype);
-  if (ws + ctrl_bytes > static_cast<size_t>(RPCA_NOALLOC_MAX_BYTES)) {
+  const size_t need = ws + ctrl_bytes - steps_bytes(static_cast<int>(rec.n), rec.geo.nb);
+  if (need > static_cast<size_t>(RPCA_NOALLOC_MAX_BYTES)) {
     char msg[200];
     std::snprintf(msg, sizeof(msg),
                   "rpca_solve_noalloc: the solve needs %zu bytes of workspace, more than the "
                   "%zu bytes of the static scratch (RPCA_NOALLOC_MAX_BYTES)",
-                  ws + ctrl_bytes, static_cast<size_t>(RPCA_NOALLOC_MAX_BYTES));
+                  need, static_cast<size_t>(RPCA_NOALLOC_MAX_BYTES));
     set_error_text(msg);
     return RPCA_ERR_ARG;
   }
