@@ -808,8 +808,11 @@ int lease_lanes(int dev, int nlanes, int count, LaneLease& lease, Lanes& view) {
 
 // Whole-solve kernel (resident_impl.h): chosen for a single solve on the
 // register kernel with one tile per slot whose tiles fit the device's CUs, two
-// per workgroup, or four for FP32 windows of up to 20 frames.  Measured at 512 x
-// 512 x 20 (FP32) and 128 x 128 x 20 (FP64): see resident_impl.h.
+// per workgroup, or four for FP32 windows of up to 20 frames: that is what fits
+// the registers.  Iteration in the kernel / launched (us): 512 x 512 x 20 FP32
+// 36 / 49, 128 x 128 x 20 FP64 25 / 39; 60 of 338 x 260 x 20 FP32 1.6 / 3.0 ms.  With kernel
+// timing on, and while another such solve runs on the device (the second one's
+// workgroups would wait for the first one's CUs), the launches are used.
 constexpr int kResidentMaxIt = 20000;  // bounds one launch (about half a second)
 constexpr int kNotRun = INT32_MIN;     // run_resident: take the launched path
 std::mutex g_resident_mu[64];          // one such solve at a time per device
