@@ -54,10 +54,10 @@ constexpr int kEigIncMaxN = 136;
 
 // Row sum of tangents at which a first eigensolve goes over to the steps.  A
 // sweep takes 230 (500) us at 100 (132) frames, a step about 30; whole solves of
-// 40 iterations, sweeps to the end / 0.9, and no tangent above 0.25 / 2: 14.64 /
-// 14.55 / 13.96 ms at 512 x 512 x 100, 24.69 / 24.22 / 22.38 at 132, and 10.03 /
-// 9.61 / 9.35 for 20 iterations of 251 x 383 x 97 FP64.
-constexpr float kStartRowSum = 2.0f;
+// 40 iterations, sweeps to the end / 0.9, and no tangent above 0.25 / 2 / 5:
+// 14.6 / 14.5 / 14.0 / 13.9 ms at 512 x 512 x 100, 24.7 / 24.2 / 22.7 / 21.3 at
+// 132, and 10.0 / 9.6 / 9.35 / 9.2 for 20 iterations of 251 x 383 x 97 FP64.
+constexpr float kStartRowSum = 5.0f;
 
 __device__ inline int pk(int i, int j) {  // packed upper index, i <= j
   return j * (j + 1) / 2 + i;
