@@ -214,6 +214,22 @@ void rpca_profile_enable(int on);
 /* Copy the accumulated figures to *out; reset them when reset != 0. */
 int rpca_profile_read(rpca_profile* out, int reset);
 
+/* Fault injection for tests of the failure handling: waits inside the kernels
+ * that the calling thread launches from then on (workgroups of one launch
+ * waiting for each other) end after `seconds` at most instead of the library's
+ * own bounds (5 ms for the workgroups of a launch to be placed, 200 ms later
+ * on); < 0 restores those.  0 makes nearly every such wait give up, as if the
+ * GPU were taken away in the middle of a launch.  Returns RPCA_OK, or
+ * RPCA_ERR_ARG for NaN. */
+int rpca_inject_wait(double seconds);
+
+/* How the calling thread's last rpca_solve_f32 / _f64 / _ex / _many ran (for
+ * tests; the results do not depend on it): the sum of */
+#define RPCA_RUN_WHOLE      1  /* in one launch, all iterations in the kernel */
+#define RPCA_RUN_WHOLE_LOST 2  /* ... that gave up a wait: run again by launches */
+#define RPCA_RUN_TEAM_LOST  4  /* above 64 frames: an eigensolver team gave one up */
+int rpca_last_run(void);
+
 /*
  * Tuning knobs (process-wide; they apply to calls started afterwards).
  *

@@ -30,6 +30,9 @@ RPCA_KNOB_EIG_THREADS = 1
 RPCA_KNOB_STREAM_KERNEL = 2
 RPCA_KNOB_TILE_ROWS = 3
 RPCA_KNOB_REG_TILES = 4
+RPCA_RUN_WHOLE = 1
+RPCA_RUN_WHOLE_LOST = 2
+RPCA_RUN_TEAM_LOST = 4
 RPCA_SERVER_SIMULATE = 1
 RPCA_SERVER_STAGE_INIT = 1
 RPCA_NOALLOC_MAX_BYTES = 192 << 20
@@ -38,7 +41,7 @@ EXPORTS = (
     "rpca_solve_f64", "rpca_solve_f32", "rpca_solve_many", "rpca_solve_ex", "rpca_solve_noalloc",
     "rpca_footprint_bytes", "rpca_strerror", "rpca_version",
     "rpca_profile_enable", "rpca_profile_read", "rpca_last_error",
-    "rpca_tune_set", "rpca_tune_get",
+    "rpca_tune_set", "rpca_tune_get", "rpca_inject_wait", "rpca_last_run",
     "rpca_server_create", "rpca_server_submit", "rpca_server_step", "rpca_server_pending",
     "rpca_server_peak_bytes", "rpca_server_request_bytes", "rpca_server_destroy",
     "rpca_server_set_timeout", "rpca_server_inject_failure",
@@ -135,6 +138,10 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.rpca_profile_enable.restype = None
     lib.rpca_profile_read.argtypes = [ctypes.POINTER(RpcaProfile), ctypes.c_int]
     lib.rpca_profile_read.restype = ctypes.c_int
+    lib.rpca_inject_wait.argtypes = [dbl]
+    lib.rpca_inject_wait.restype = ctypes.c_int
+    lib.rpca_last_run.argtypes = []
+    lib.rpca_last_run.restype = ctypes.c_int
     lib.rpca_tune_set.argtypes = [i32, i32, i32, i32]
     lib.rpca_tune_set.restype = ctypes.c_int
     lib.rpca_tune_get.argtypes = [i32, i32, i32]

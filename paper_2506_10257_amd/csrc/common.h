@@ -41,6 +41,7 @@ struct SolveState {
   int32_t sweeps;                   // Jacobi sweeps of the last eigensolve
   int32_t sweeps_total;             // over the whole solve
   int32_t warm_stage;               // given start: 0 norms pending, 1 Gram of A_1 pending, 2 running
+  int32_t lost;                     // launches of the wide steps in which a workgroup gave up waiting
   int64_t trace[8];                 // phase times of the eigensolve (trace builds only)
 };
 
@@ -124,8 +125,9 @@ constexpr int kWideSteps = 9;       // simultaneous steps of a launch at most
 constexpr int kWideMats = 12;       // G, W, S, K, T, U, C, Z, two more V, two V^T
 constexpr int kWideCtlDoubles = 32;
 struct WideCtl {
-  int32_t booked;  // the iteration whose P the steps wrote last (0: none)
+  int32_t booked;  // the iteration whose P the launch's steps wrote (0: none)
   int32_t vsel;    // which of the three V buffers holds V
+  int32_t vnext;   // ... once the booked iteration stands
   // the steps' workgroups of one launch; zero between launches
   uint32_t arrived;                  // meetings, counted by workgroup
   uint32_t lost;                     // a workgroup gave up waiting

@@ -32,13 +32,17 @@
 // kTeamGroups workgroups between them.  The blocks are computed alike however
 // many workgroups there are, so the results have the same bits.
 //
-// A workgroup waits for its team at every meeting, for kTeamTicks at most; then
-// it gives up, all others follow, and the Jacobi kernel does the iteration.
+// A workgroup waits for its team at every meeting, for a bounded time (launch.h);
+// then it gives up, the others follow at this meeting or a later one, and the
+// Jacobi kernel, which runs after all of them have ended, does the iteration.
+// Until then nothing that the next iteration reads is changed: the Jacobi kernel
+// advances the iteration and V where nobody gave up.
 #include <algorithm>
 
 #include "common.h"
 #include "eig_common.h"
 #include "launch.h"
+#include "team.h"
 
 namespace rpca {
 namespace {
@@ -64,12 +68,27 @@ __device__ inline void st_to(gptr<T> p, T v) {
   else *p = v;
 }
 
+struct TeamCtl {  // one workgroup's view of its team (see team.h)
+  WideCtl* ctl;
+  int64_t until;
+  __device__ void arrive() {
+    __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ unsigned arrived() const {
+    return __hip_atomic_load(&ctl->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ bool lost() const {
+    return __hip_atomic_load(&ctl->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+  }
+  __device__ bool late() const { return wall_clock64() > until; }
+  __device__ void lose() { __hip_atomic_store(&ctl->lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
+
 // All workgroups of a team, each at its meeting number `meeting` (1, 2, ...):
 // what any of them stored before is seen by all after.  False when one of them
-// did not come in time (kTeamTicks of the 100 MHz wall clock).
-constexpr int64_t kTeamTicks = 20000000;  // 200 ms
+// did not come in time (`ticks` of the 100 MHz wall clock).
 template <bool TEAM>
-__device__ inline bool meet(WideCtl* ctl, unsigned meeting, int* s_ok) {
+__device__ inline bool meet(WideCtl* ctl, unsigned meeting, int64_t ticks, int* s_ok) {
   if constexpr (!TEAM) {
     __syncthreads();
     return true;
@@ -78,19 +97,8 @@ __device__ inline bool meet(WideCtl* ctl, unsigned meeting, int* s_ok) {
     __syncthreads();
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned all = meeting * gridDim.x;
-      const int64_t until = wall_clock64() + kTeamTicks;
-      int ok = 1;
-      while (__hip_atomic_load(&ctl->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
-        if (__hip_atomic_load(&ctl->lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) ok = 0;
-        if (ok && wall_clock64() > until) {
-          __hip_atomic_store(&ctl->lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ok = 0;
-        }
-        if (!ok) break;
-      }
-      *s_ok = ok;
+      TeamCtl c{ctl, wall_clock64() + ticks};
+      *s_ok = meet_team(c, meeting * gridDim.x) ? 1 : 0;
     }
     __syncthreads();
     return *s_ok != 0;
@@ -255,7 +263,7 @@ __device__ inline d4 load_block(const double* M, int nb, int bi, int bj) {
 
 template <typename T, bool TEAM>
 __global__ void __launch_bounds__(kStepThreads)
-k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
+k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids, int64_t ticks) {
   __shared__ double dg[kEigHugeMaxN], sg[kEigHugeMaxN], w[kEigHugeMaxN], sd[kEigHugeMaxN];
   __shared__ double tbuf[kStepWaves][16 * kTrLd];
   __shared__ double scal[kScalars];
@@ -327,7 +335,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     }
   }
   if (tid < 8) mx[tid >> 2][tid & 3] = 0u;
-  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
   if (tid == 0 && g == 0) {  // its scalars are this workgroup's own
     double t = pf_tau;
     s_go = kd == 0 ? 1 : control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);  // kd = 0: done there
@@ -355,7 +363,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const double* V = e.v(v0);
   int u = gw;
   product<TEAM, false>(u, nw, e.G, V, nb, put(e.W));
-  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
   if constexpr (TEAM) {
     if (tid == 0) {
       s_tau = __hip_atomic_load(&e.ctl->tau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -373,7 +381,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     const int bi = t / nt, bj = t - bi * nt;
     store_block<TEAM>(e.vt(0), nb, bj, bi, transposed(load_block<TEAM>(V, nb, bi, bj), tb));
   }
-  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
 
   STEP_MARK(2);
   int s = 0;
@@ -428,7 +436,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       unsigned* all = e.ctl->mx[s];
       if (tid < 4 && mp[tid] != 0u)
         __hip_atomic_fetch_max(&all[tid], mp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+      if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
       if (tid < 4) mp[tid] = __hip_atomic_load(&all[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
@@ -461,7 +469,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     } else {
       product<TEAM, true>(u, nw, e.K, e.K, nb,
                     [&](int bi, int bj, const d4& v) { store_mirrored<TEAM>(e.T, nb, bi, bj, -v, zero, tb); });
-      if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+      if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
       // K T = -K^T T into W, then T^2 and U (a block of both has one owner)
       u = gw;
       product<TEAM, true>(u, nw, e.K, e.T, nb, [&](int bi, int bj, const d4& v) { store_block<TEAM>(e.W, nb, bi, bj, -v); });
@@ -472,7 +480,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
         store_mirrored<TEAM>(e.U, nb, bi, bj, h, k, tb);
       });
     }
-    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
     // W = S U, V' = V U (and its transpose);  S = U^T W, C = V'^T V'
     double* Vn = e.v(WideEig::vsel(v0, s + 1));
     u = gw;
@@ -482,11 +490,11 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       store_block<TEAM>(e.vt((s + 1) & 1), nb, bj, bi, transposed(v, tb));
     });
     V = Vn;
-    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
     u = gw;
     product<TEAM, true>(u, nw, e.U, e.W, nb, put_sym(e.S));
     product<TEAM, true>(u, nw, V, V, nb, put(e.C));
-    if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
     STEP_MARK(2);
   }
   if (!ok) return;  // the Jacobi kernel takes over, from V at v0
@@ -495,21 +503,21 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const double* Vt = e.vt(s & 1);
   u = gw;
   product<TEAM, false>(u, nw, e.Z, Vt, nb, put(e.W));
-  if (!meet<TEAM>(e.ctl, ++meeting, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
   u = gw;
   product<TEAM, true>(u, nw, Vt, e.W, nb, [&](int bi, int bj, const d4& v) {
     store_mirrored<false>(static_cast<T*>(d.P), nb, bi, bj, v, zero, tb);
   });
   const int rank = __syncthreads_count(tid < n && w[tid] != 0.0);
   if (tid == 0 && g == 0) {
-    e.ctl->vsel = WideEig::vsel(v0, s);
+    // the Jacobi kernel makes it this iteration's, if it stands
+    e.ctl->vnext = WideEig::vsel(v0, s);
     e.ctl->booked = kd + 1;
     st->rank = rank;
     st->sweeps = 0;
 #ifdef RPCA_TRACE
     st->sweeps_total += s;
 #endif
-    st->iter = kd + 1;
   }
   STEP_MARK(3);
 #undef STEP_MARK
@@ -535,13 +543,13 @@ hipError_t launch_eig_steps(int dtype, int grid, int team, hipStream_t stream, c
   if (grid <= 0) return hipSuccess;
   const dim3 g(team, grid), b(kStepThreads);
   if (dtype == 1 && team > 1)
-    RPCA_LAUNCH((k_eig_steps<float, true>), g, b, 0, stream, descs, ids);
+    RPCA_LAUNCH((k_eig_steps<float, true>), g, b, 0, stream, descs, ids, t_limits.wait_ticks);
   else if (dtype == 1)
-    RPCA_LAUNCH((k_eig_steps<float, false>), g, b, 0, stream, descs, ids);
+    RPCA_LAUNCH((k_eig_steps<float, false>), g, b, 0, stream, descs, ids, t_limits.wait_ticks);
   else if (team > 1)
-    RPCA_LAUNCH((k_eig_steps<double, true>), g, b, 0, stream, descs, ids);
+    RPCA_LAUNCH((k_eig_steps<double, true>), g, b, 0, stream, descs, ids, t_limits.wait_ticks);
   else
-    RPCA_LAUNCH((k_eig_steps<double, false>), g, b, 0, stream, descs, ids);
+    RPCA_LAUNCH((k_eig_steps<double, false>), g, b, 0, stream, descs, ids, t_limits.wait_ticks);
   return hipGetLastError();
 }
 

@@ -42,6 +42,7 @@
 #include "common.h"
 #include "eig_common.h"
 #include "launch.h"
+#include "team.h"
 
 namespace rpca {
 namespace {
@@ -114,13 +115,24 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
   const int nb = d.nb;
   const int kd = st->iter;
   const WideEig we(d);
-  if (tid == 0) {  // for the steps' next launch
-    we.ctl->arrived = 0u;
-    we.ctl->lost = 0u;
-  }
-  if (tid < (kWideSteps + 1) * 4) we.ctl->mx[tid >> 2][tid & 3] = 0u;
+  const uint32_t lost = start ? 0u : we.ctl->lost;
+  const bool booked = !start && steps_stand(lost, we.ctl->booked, kd + 1);
   // a solve's first eigensolve that the steps did not finish: as a later one
   const bool handed = kd == 0 && !start && we.ctl->ready != 0u;
+  __syncthreads();  // every thread has read what thread 0 writes
+  if (tid == 0) {   // for the steps' next launch
+    we.ctl->arrived = 0u;
+    we.ctl->lost = 0u;
+    if (lost != 0u) ++st->lost;
+  }
+  if (tid < (kWideSteps + 1) * 4) we.ctl->mx[tid >> 2][tid & 3] = 0u;
+  if (booked) {  // the steps (eig_steps.hip) wrote this iteration's P
+    if (tid == 0) {
+      we.ctl->vsel = we.ctl->vnext;
+      st->iter = kd + 1;
+    }
+    return;
+  }
   if (kd == 0 && !handed) {
     // the steps' matrices are zero outside n x n, and V is in its first buffer
     const int len = kWideMats * nb * nb;
@@ -130,8 +142,6 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
       we.ctl->vsel = 0;
       we.ctl->ready = 0u;
     }
-  } else if (kd > 0 && we.ctl->booked == kd) {
-    return;  // the steps (eig_steps.hip) wrote this iteration's P
   }
   double* const dV = kd == 0 ? d.V : we.v(we.ctl->vsel);
   // read now (thread 0 runs the control step), in flight during the reduction

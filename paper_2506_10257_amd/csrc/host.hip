@@ -38,6 +38,7 @@
 namespace rpca {
 
 thread_local LaunchEvents t_launch_events;
+thread_local RunLimits t_limits;
 
 namespace {
 
@@ -48,6 +49,7 @@ constexpr int kDirectChunkMax = 64;
 size_t al256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 thread_local char g_last_error[512] = "";
+thread_local int g_last_run = 0;  // rpca_last_run
 
 // ---------------------------------------------------------------- profiling
 struct EvPair {
@@ -896,6 +898,8 @@ int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hi
   rb.sums = reinterpret_cast<uint64_t*>(mem + head + parts);
   rb.tpw = rp.tpw;
   rb.ushift = rp.ushift;
+  rb.arrive_ticks = t_limits.arrive_ticks;
+  rb.wait_ticks = t_limits.wait_ticks;
   e = launch_zero(reinterpret_cast<uint64_t*>(mem), (head + parts + sums) / sizeof(uint64_t), s);
   if (e == hipSuccess)
     e = dtype == RPCA_F32 ? launch_resident_f32(rp.nb, rp.threads, rp.grid, s, d, rb)
@@ -920,7 +924,11 @@ int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hi
                st.trace[0] * 0.01 / st.iter, st.trace[1] * 0.01 / st.iter, st.trace[2] * 0.01 / st.iter,
                st.trace[3] * 0.01 / st.iter, st.trace[4] * 0.01 / st.iter, st.trace[5] * 0.01 / st.iter, lost);
 #endif
-  if (lost != 0) return kNotRun;  // a wait ran out of time: nothing was kept
+  if (lost != 0) {  // a wait ran out of time: nothing is kept
+    g_last_run |= RPCA_RUN_WHOLE_LOST;
+    return kNotRun;
+  }
+  g_last_run |= RPCA_RUN_WHOLE;
   prob.iterations = st.iter;
   prob.status = st.status;
   prob.residual = st.resid;
@@ -929,6 +937,7 @@ int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hi
 
 int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream_t user) {
   g_last_error[0] = '\0';
+  g_last_run = 0;
   if (count < 1 || probs == nullptr) return RPCA_ERR_ARG;
   if (dtype != RPCA_F32 && dtype != RPCA_F64) return RPCA_ERR_ARG;
   if (gram_mode != RPCA_GRAM_DEFAULT && gram_mode != RPCA_GRAM_BF16X3 &&
@@ -1079,6 +1088,7 @@ int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStrea
     for (int i = 0; i < count; ++i) {
       const SolveState& st = L.pinned[0][i];
       recs[i].st = st;
+      if (st.lost > 0) g_last_run |= RPCA_RUN_TEAM_LOST;
       probs[i].iterations = st.iter;
       probs[i].status = st.status;
       probs[i].residual = st.resid;
@@ -1279,6 +1289,19 @@ int rpca_tune_get(int32_t knob, int32_t dtype, int32_t cls) {
 }
 
 const char* rpca_last_error(void) { return g_last_error; }
+
+int rpca_last_run(void) { return g_last_run; }
+
+int rpca_inject_wait(double seconds) {
+  if (std::isnan(seconds)) return RPCA_ERR_ARG;
+  t_limits = RunLimits{};
+  if (seconds >= 0.0) {
+    const int64_t ticks = static_cast<int64_t>(std::min(seconds, 1.0) * 1e8);
+    t_limits.arrive_ticks = std::min(t_limits.arrive_ticks, ticks);
+    t_limits.wait_ticks = std::min(t_limits.wait_ticks, ticks);
+  }
+  return RPCA_OK;
+}
 
 void rpca_profile_enable(int on) {
   std::lock_guard<std::mutex> lk(g_prof.mu);

@@ -17,6 +17,17 @@ struct LaunchEvents {
 };
 extern thread_local LaunchEvents t_launch_events;
 
+// Bounds of the waits inside a launch, in ticks of the 100 MHz wall clock: at the
+// whole-solve kernel's first exchange (workgroups still being placed), and at its
+// later ones and the meetings of the eigensolver's teams (all are running).  Per
+// host thread, so that a test can end its own calls' waits early
+// (rpca_inject_wait).
+struct RunLimits {
+  int64_t arrive_ticks = 500000;   // 5 ms
+  int64_t wait_ticks = 20000000;   // 200 ms
+};
+extern thread_local RunLimits t_limits;
+
 #define RPCA_LAUNCH(K, G, B, SH, S, ...)                                                      \
   do {                                                                                       \
     if (::rpca::t_launch_events.start || ::rpca::t_launch_events.stop)                       \
@@ -87,6 +98,7 @@ struct ResidentBuf {
   uint32_t* lost;   // set when a wait ran out of time
   int32_t tpw;      // 256-row tiles per workgroup (1, 2 or 4)
   int32_t ushift;   // log2 of the workgroup count, rounded up
+  int64_t arrive_ticks, wait_ticks;  // bounds of a wait (RunLimits)
 };
 hipError_t launch_resident_f32(int nb, int threads, int grid, hipStream_t stream, const SolveDesc& d,
                                const ResidentBuf& rb);

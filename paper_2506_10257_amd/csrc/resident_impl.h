@@ -48,11 +48,6 @@
 namespace rpca {
 namespace {
 
-// Wall clock ticks (100 MHz): first exchange (workgroups still being placed),
-// later ones (all are running).
-constexpr int64_t kArriveTicks = 500000;   // 5 ms
-constexpr int64_t kWaitTicks = 20000000;   // 200 ms
-
 __device__ inline void ll_store(uint64_t* cell, uint32_t seq, double v) {
   const uint64_t b = __builtin_bit_cast(uint64_t, v), s = static_cast<uint64_t>(seq) << 32;
   __hip_atomic_store(cell, s | (b & 0xffffffffu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -305,7 +300,7 @@ k_resident(const SolveDesc d, const ResidentBuf rb) {
     }
     RES_MARK(3);
     // 2. entries blockIdx.x, blockIdx.x + grid, ...: `per` of them at a time
-    const int64_t ticks = seq == 1 ? kArriveTicks : kWaitTicks;
+    const int64_t ticks = seq == 1 ? rb.arrive_ticks : rb.wait_ticks;
     const int per = NT >> rb.ushift, groups = (d.tiles + kGroup - 1) / kGroup, upad = 1 << rb.ushift;
     bool lost = false;
     for (int base = blockIdx.x; base < nent; base += grid * per) {
