@@ -25,6 +25,7 @@ constexpr int kScalars = 4;        // scalar slots at the head of each partial
 constexpr int kOk = 0;
 constexpr int kNotConverged = 1;
 constexpr int kErrNonfinite = -4;
+constexpr int kLostTeam = -100;  // internal: a wide eigensolver team gave up waiting; the host runs the solve again
 
 // Per-solve iteration state, written only by device code once the solve runs.
 struct SolveState {
@@ -41,7 +42,6 @@ struct SolveState {
   int32_t sweeps;                   // Jacobi sweeps of the last eigensolve
   int32_t sweeps_total;             // over the whole solve
   int32_t warm_stage;               // given start: 0 norms pending, 1 Gram of A_1 pending, 2 running
-  int32_t lost;                     // launches of the wide steps in which a workgroup gave up waiting
   int64_t trace[8];                 // phase times of the eigensolve (trace builds only)
 };
 
@@ -68,6 +68,7 @@ struct SolveDesc {
   int32_t pstride;        // doubles per partial slot
   int32_t maxit;
   int32_t warm;           // 1 when the solve starts from a given S0 / Y0
+  int32_t alone;          // 1: one workgroup in the wide eigensolver's steps, whatever the launch
   double lam_in, mu_in, tol;
 };
 

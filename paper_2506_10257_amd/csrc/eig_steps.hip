@@ -33,10 +33,10 @@
 // many workgroups there are, so the results have the same bits.
 //
 // A workgroup waits for its team at every meeting, for a bounded time (launch.h);
-// then it gives up, the others follow at this meeting or a later one, and the
-// Jacobi kernel, which runs after all of them have ended, does the iteration.
-// Until then nothing that the next iteration reads is changed: the Jacobi kernel
-// advances the iteration and V where nobody gave up.
+// then it gives up and the others follow at this meeting or a later one.  The
+// Jacobi kernel, which runs after all of them have ended, advances the iteration
+// and V where nobody gave up; else it ends the solve, and the host runs it again
+// from its inputs with one workgroup (`alone`), which waits for nobody.
 #include <algorithm>
 
 #include "common.h"
@@ -84,11 +84,11 @@ struct TeamCtl {  // one workgroup's view of its team (see team.h)
   __device__ void lose() { __hip_atomic_store(&ctl->lost, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
-// All workgroups of a team, each at its meeting number `meeting` (1, 2, ...):
-// what any of them stored before is seen by all after.  False when one of them
-// did not come in time (`ticks` of the 100 MHz wall clock).
+// All workgroups of a team at a meeting, complete with `all` arrivals since the
+// launch began: what any of them stored before is seen by all after.  False when
+// one of them did not come in time (`ticks` of the 100 MHz wall clock).
 template <bool TEAM>
-__device__ inline bool meet(WideCtl* ctl, unsigned meeting, int64_t ticks, int* s_ok) {
+__device__ inline bool meet(WideCtl* ctl, unsigned all, int64_t ticks, int* s_ok) {
   if constexpr (!TEAM) {
     __syncthreads();
     return true;
@@ -98,7 +98,7 @@ __device__ inline bool meet(WideCtl* ctl, unsigned meeting, int64_t ticks, int* 
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       TeamCtl c{ctl, wall_clock64() + ticks};
-      *s_ok = meet_team(c, meeting * gridDim.x) ? 1 : 0;
+      *s_ok = meet_team(c, all) ? 1 : 0;
     }
     __syncthreads();
     return *s_ok != 0;
@@ -295,8 +295,10 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   double pf_nXF2 = 0.0, pf_tau = 0.0;
   // workgroup g of the solve's team; thread and wave of the whole team
   const int g = TEAM ? blockIdx.x : 0;
-  const int teams = TEAM ? gridDim.x : 1, nw = teams * kStepWaves, gtid = g * kStepThreads + tid;
-  unsigned meeting = 0;
+  const int teams = TEAM && !d.alone ? gridDim.x : 1;
+  if (g >= teams) return;
+  const int nw = teams * kStepWaves, gtid = g * kStepThreads + tid;
+  unsigned all = 0;  // arrivals that complete the next meeting
   if (tid == 0 && g == 0) {
     pf_nXF2 = st->nXF2;
     pf_tau = st->tau;
@@ -335,7 +337,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     }
   }
   if (tid < 8) mx[tid >> 2][tid & 3] = 0u;
-  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
   if (tid == 0 && g == 0) {  // its scalars are this workgroup's own
     double t = pf_tau;
     s_go = kd == 0 ? 1 : control_step(d, st, scal, kd, pf_nXF2, pf_tau, t);  // kd = 0: done there
@@ -363,7 +365,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const double* V = e.v(v0);
   int u = gw;
   product<TEAM, false>(u, nw, e.G, V, nb, put(e.W));
-  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
   if constexpr (TEAM) {
     if (tid == 0) {
       s_tau = __hip_atomic_load(&e.ctl->tau, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -381,7 +383,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     const int bi = t / nt, bj = t - bi * nt;
     store_block<TEAM>(e.vt(0), nb, bj, bi, transposed(load_block<TEAM>(V, nb, bi, bj), tb));
   }
-  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
 
   STEP_MARK(2);
   int s = 0;
@@ -433,11 +435,11 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     wave_max_to(mt, &mp[3]);
     if constexpr (TEAM) {
       __syncthreads();
-      unsigned* all = e.ctl->mx[s];
+      unsigned* top = e.ctl->mx[s];
       if (tid < 4 && mp[tid] != 0u)
-        __hip_atomic_fetch_max(&all[tid], mp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
-      if (tid < 4) mp[tid] = __hip_atomic_load(&all[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_max(&top[tid], mp[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
+      if (tid < 4) mp[tid] = __hip_atomic_load(&top[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     mz = __uint_as_float(mp[0]);
@@ -469,7 +471,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     } else {
       product<TEAM, true>(u, nw, e.K, e.K, nb,
                     [&](int bi, int bj, const d4& v) { store_mirrored<TEAM>(e.T, nb, bi, bj, -v, zero, tb); });
-      if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+      if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
       // K T = -K^T T into W, then T^2 and U (a block of both has one owner)
       u = gw;
       product<TEAM, true>(u, nw, e.K, e.T, nb, [&](int bi, int bj, const d4& v) { store_block<TEAM>(e.W, nb, bi, bj, -v); });
@@ -480,7 +482,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
         store_mirrored<TEAM>(e.U, nb, bi, bj, h, k, tb);
       });
     }
-    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
     // W = S U, V' = V U (and its transpose);  S = U^T W, C = V'^T V'
     double* Vn = e.v(WideEig::vsel(v0, s + 1));
     u = gw;
@@ -490,11 +492,11 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       store_block<TEAM>(e.vt((s + 1) & 1), nb, bj, bi, transposed(v, tb));
     });
     V = Vn;
-    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
     u = gw;
     product<TEAM, true>(u, nw, e.U, e.W, nb, put_sym(e.S));
     product<TEAM, true>(u, nw, V, V, nb, put(e.C));
-    if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+    if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
     STEP_MARK(2);
   }
   if (!ok) return;  // the Jacobi kernel takes over, from V at v0
@@ -503,7 +505,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const double* Vt = e.vt(s & 1);
   u = gw;
   product<TEAM, false>(u, nw, e.Z, Vt, nb, put(e.W));
-  if (!meet<TEAM>(e.ctl, ++meeting, ticks, &s_ok)) return;
+  if (!meet<TEAM>(e.ctl, all += teams, ticks, &s_ok)) return;
   u = gw;
   product<TEAM, true>(u, nw, Vt, e.W, nb, [&](int bi, int bj, const d4& v) {
     store_mirrored<false>(static_cast<T*>(d.P), nb, bi, bj, v, zero, tb);

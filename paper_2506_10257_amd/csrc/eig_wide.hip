@@ -115,16 +115,22 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
   const int nb = d.nb;
   const int kd = st->iter;
   const WideEig we(d);
-  const uint32_t lost = start ? 0u : we.ctl->lost;
-  const bool booked = !start && steps_stand(lost, we.ctl->booked, kd + 1);
+  const bool lost = !start && we.ctl->lost != 0u;
+  const bool booked = !start && steps_stand(we.ctl->lost, we.ctl->booked, kd + 1);
   // a solve's first eigensolve that the steps did not finish: as a later one
   const bool handed = kd == 0 && !start && we.ctl->ready != 0u;
   __syncthreads();  // every thread has read what thread 0 writes
   if (tid == 0) {   // for the steps' next launch
     we.ctl->arrived = 0u;
     we.ctl->lost = 0u;
-    if (lost != 0u) ++st->lost;
+    if (lost) {
+      // sweeps from here would round differently from the steps: the host runs
+      // the solve again with one workgroup, so its bits do not depend on time
+      st->status = kLostTeam;
+      st->done = 1;
+    }
   }
+  if (lost) return;
   if (tid < (kWideSteps + 1) * 4) we.ctl->mx[tid >> 2][tid & 3] = 0u;
   if (booked) {  // the steps (eig_steps.hip) wrote this iteration's P
     if (tid == 0) {

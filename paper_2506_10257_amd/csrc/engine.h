@@ -52,6 +52,7 @@ struct SolveRec {
   const void* S0 = nullptr;    // optional starting S
   const void* Y0 = nullptr;    // optional starting Y
   int warm = 0;                // starts from S0 / Y0
+  int alone = 0;               // eigensolver teams of one workgroup (run again after a lost team)
   int64_t m = 0;
   int32_t n = 0;
   double lam = -1.0, mu = -1.0, tol = 0.0;

@@ -426,6 +426,7 @@ size_t plan_prepare(Plan& plan, const std::vector<SolveRec*>& recs, int nlanes, 
     d.S0 = r.S0;
     d.Y0 = r.Y0;
     d.warm = r.warm;
+    d.alone = r.alone;
     d.partials = reinterpret_cast<double*>(b + r.big.part);
     d.gpartials = reinterpret_cast<double*>(b + r.big.gpart);
     d.P = b + r.big.P;
@@ -935,9 +936,9 @@ int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hi
   return st.status;
 }
 
-int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream_t user) {
-  g_last_error[0] = '\0';
-  g_last_run = 0;
+// One pass over the problems; kLostTeam where a wide eigensolver team gave up
+// waiting (the status of each such problem says so too).  alone: teams of one.
+int run_pass(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream_t user, bool alone) {
   if (count < 1 || probs == nullptr) return RPCA_ERR_ARG;
   if (dtype != RPCA_F32 && dtype != RPCA_F64) return RPCA_ERR_ARG;
   if (gram_mode != RPCA_GRAM_DEFAULT && gram_mode != RPCA_GRAM_BF16X3 &&
@@ -949,6 +950,7 @@ int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStrea
   for (int i = 0; i < count; ++i) {
     const int vrc = make_rec(probs[i], dtype, gram_mode, recs[i]);
     if (vrc != RPCA_OK) return vrc;
+    recs[i].alone = alone ? 1 : 0;
   }
 
   // Lanes: balance the matrix sizes, largest first.  Kernel timing runs on
@@ -1088,7 +1090,7 @@ int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStrea
     for (int i = 0; i < count; ++i) {
       const SolveState& st = L.pinned[0][i];
       recs[i].st = st;
-      if (st.lost > 0) g_last_run |= RPCA_RUN_TEAM_LOST;
+      if (st.status == kLostTeam) g_last_run |= RPCA_RUN_TEAM_LOST;
       probs[i].iterations = st.iter;
       probs[i].status = st.status;
       probs[i].residual = st.resid;
@@ -1173,6 +1175,36 @@ done:
 }
 
 #undef CK
+
+// All passes: problems that lost a team run again from their (unchanged) inputs,
+// without waits.
+int run_batch(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream_t user) {
+  g_last_error[0] = '\0';
+  g_last_run = 0;
+  int rc = run_pass(probs, count, dtype, gram_mode, user, false);
+  if (rc != kLostTeam) return rc;
+  std::vector<int> which;
+  std::vector<rpca_problem> again;
+  for (int i = 0; i < count; ++i)
+    if (probs[i].status == kLostTeam) {
+      which.push_back(i);
+      again.push_back(probs[i]);
+    }
+  rc = run_pass(again.data(), static_cast<int>(again.size()), dtype, gram_mode, user, true);
+  for (size_t k = 0; k < which.size(); ++k) {
+    rpca_problem& p = probs[which[k]];
+    p.iterations = again[k].iterations;
+    p.status = again[k].status == kLostTeam ? rc : again[k].status;  // not run: the pass's own error
+    p.residual = again[k].residual;
+  }
+  if (rc < 0) return rc;
+  int worst_neg = 0, any_nc = 0;
+  for (int i = 0; i < count; ++i) {
+    worst_neg = std::min(worst_neg, probs[i].status);
+    if (probs[i].status == RPCA_NOT_CONVERGED) any_nc = 1;
+  }
+  return worst_neg < 0 ? worst_neg : (any_nc ? RPCA_NOT_CONVERGED : RPCA_OK);
+}
 
 }  // namespace
 
@@ -1296,7 +1328,7 @@ int rpca_inject_wait(double seconds) {
   if (std::isnan(seconds)) return RPCA_ERR_ARG;
   t_limits = RunLimits{};
   if (seconds >= 0.0) {
-    const int64_t ticks = static_cast<int64_t>(std::min(seconds, 1.0) * 1e8);
+    const int64_t ticks = seconds == 0.0 ? -1 : static_cast<int64_t>(std::min(seconds, 1.0) * 1e8);
     t_limits.arrive_ticks = std::min(t_limits.arrive_ticks, ticks);
     t_limits.wait_ticks = std::min(t_limits.wait_ticks, ticks);
   }

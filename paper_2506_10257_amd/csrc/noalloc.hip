@@ -129,25 +129,31 @@ int solve_noalloc(const rpca_problem& p, int dtype, hipStream_t stream, int32_t*
   {
     // the caller's stream orders the previous call's work (and the inputs)
     // before this one's use of the array
-    rc = plan_upload(plan, base + ws, stream);
-    if (rc != RPCA_OK) goto done;
-    NA(enqueue_reset_states(plan, stream));
-    NA(enqueue_init(plan, L));
-    int launched = 0, chunk = kChunkFirst;
     for (;;) {
-      // a solve that stops after k passes needs k + 1 eigensolve launches
-      // (the last one records the stop); at most maxit + 1
-      const int c = std::min(chunk, rec.maxit + 1 - launched);
-      if (c <= 0) {
-        set_error_text("rpca_solve_noalloc: the solve did not stop after maxit + 1 launches");
-        rc = RPCA_ERR_DEVICE;
-        goto done;
+      rc = plan_upload(plan, base + ws, stream);
+      if (rc != RPCA_OK) goto done;
+      NA(enqueue_reset_states(plan, stream));
+      NA(enqueue_init(plan, L));
+      int launched = 0, chunk = kChunkFirst;
+      for (;;) {
+        // a solve that stops after k passes needs k + 1 eigensolve launches
+        // (the last one records the stop); at most maxit + 1
+        const int c = std::min(chunk, rec.maxit + 1 - launched);
+        if (c <= 0) {
+          set_error_text("rpca_solve_noalloc: the solve did not stop after maxit + 1 launches");
+          rc = RPCA_ERR_DEVICE;
+          goto done;
+        }
+        NA(enqueue_iterations(plan, L, c));
+        launched += c;
+        NA(read_state(plan, stream, st));
+        if (st.done) break;
+        chunk = std::min(chunk * 2, kChunkMax);
       }
-      NA(enqueue_iterations(plan, L, c));
-      launched += c;
-      NA(read_state(plan, stream, st));
-      if (st.done) break;
-      chunk = std::min(chunk * 2, kChunkMax);
+      if (st.status != kLostTeam) break;
+      rec.alone = 1;  // again from the inputs, without waits (eig_steps.hip)
+      plan = Plan{};
+      (void)plan_prepare(plan, recs, 1, dtype);
     }
     NA(enqueue_finalize(plan, L));
     NA(read_state(plan, stream, st));

@@ -53,12 +53,13 @@ __device__ inline void ll_store(uint64_t* cell, uint32_t seq, double v) {
   __hip_atomic_store(cell, s | (b & 0xffffffffu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(cell + 1, s | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// False when the time is over.
+// False when the time is over (ticks < 0: after one look).
 __device__ inline bool ll_wait(const uint64_t* cell, uint32_t seq, int64_t ticks, double& v) {
   const int64_t until = wall_clock64() + ticks;
+  const int most = ticks < 0 ? 1 : 64;
   for (;;) {
 #pragma unroll 1
-    for (int tries = 0; tries < 64; ++tries) {
+    for (int tries = 0; tries < most; ++tries) {
       const uint64_t a = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint64_t b = __hip_atomic_load(cell + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if ((a >> 32) == seq && (b >> 32) == seq) {

@@ -221,6 +221,8 @@ hipError_t join_to0(const Lanes& L) {
   return e;
 }
 
+int init_stage(rpca_server* s, std::vector<Req*>& ok);
+
 // Set-up of newly admitted requests: workspace, then their init pass.  On a
 // failure the requests of this stage are released (fail_admitted) before the
 // code is returned, so nothing leaks and the budget is given back.
@@ -256,6 +258,13 @@ int start_admitted(rpca_server* s, std::vector<Req*>& fresh) {
     ok.push_back(r);
   }
   fresh.clear();
+  return init_stage(s, ok);
+}
+
+// The init pass of requests that have their workspace; they become active.
+int init_stage(rpca_server* s, std::vector<Req*>& ok) {
+  Lanes& L = s->lanes;
+  hipStream_t s0 = L.s[0];
   if (ok.empty()) return RPCA_OK;
   std::vector<SolveRec*> recs = recs_of(ok);
   const int nl = nlanes_for(recs.size());
@@ -338,9 +347,10 @@ int step_device(rpca_server* s) {
 
   // 4. retire the solves that stopped, and drop those past their deadline
   const int64_t now = now_ns(s);
-  std::vector<Req*> done, late, keep;
+  std::vector<Req*> done, late, keep, again;
   for (Req* r : s->active) {
-    if (r->rec.st.done) done.push_back(r);
+    if (r->rec.st.done && r->rec.st.status == kLostTeam && !expired(s, r, now)) again.push_back(r);
+    else if (r->rec.st.done && r->rec.st.status != kLostTeam) done.push_back(r);
     else if (expired(s, r, now)) late.push_back(r);
     else keep.push_back(r);
   }
@@ -367,6 +377,7 @@ int step_device(rpca_server* s) {
       // keep them active (they exit their launches at once); retried next step
       plan_free(pd, s0);
       for (Req* r : done) keep.push_back(r);
+      for (Req* r : again) keep.push_back(r);
       s->active.swap(keep);
       return rc;
     }
@@ -391,7 +402,12 @@ int step_device(rpca_server* s) {
     s->plan_valid = false;
   }
   s->active.swap(keep);
-  return RPCA_OK;
+  // a wide eigensolver team gave up waiting: from the inputs again, without waits
+  for (Req* r : again) {
+    r->rec.alone = 1;
+    s->plan_valid = false;
+  }
+  return init_stage(s, again);
 }
 
 #undef SV
