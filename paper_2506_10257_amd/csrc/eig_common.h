@@ -245,8 +245,8 @@ __device__ inline void wave_max_to(float x, unsigned* cell) {
   if ((threadIdx.x & 63) == 0 && a != 0u) atomicMax(cell, a);
 }
 
-// sqrt(d), or 0 for d <= 0 (the rounding of a zero eigenvalue).
-__device__ inline double sqrt_or_zero(double d) { return d > kTiny2 ? d * rsqrt_pos(d) : 0.0; }
+// sqrt(d), or 0 for d <= 0 (the rounding of a zero eigenvalue); NaN for infinity.
+__device__ inline double sqrt_or_zero(double d) { return d <= kTiny2 ? 0.0 : d * rsqrt_pos(d); }
 
 // View of a wide solve's workspace (see common.h).  cls is the class of the
 // Jacobi kernel, whose scratch comes first.

@@ -315,9 +315,10 @@ __device__ __forceinline__ int eig_core(EigLds<NMAX>& sh, int n, bool warm, doub
         const int i = ui[q], j = uj[q];
         const double sii = sh.sd[i], sjj = sh.sd[j], mii = sh.md[i], mjj = sh.md[j];
         const double di = fma(-mii, sii, sii), dj = fma(-mjj, sjj, sjj);
-        const double ri = di > kTiny2 ? rsqrt_pos(di) : 0.0, rj = dj > kTiny2 ? rsqrt_pos(dj) : 0.0;
+        // (the Gram overflowed: NaN from here into P, and the solve says so)
+        const double ri = di <= kTiny2 ? 0.0 : rsqrt_pos(di), rj = dj <= kTiny2 ? 0.0 : rsqrt_pos(dj);
         const double si = di * ri, sj = dj * rj;
-        const double wi = si > tau ? fma(-tau, ri, 1.0) : 0.0, wj = sj > tau ? fma(-tau, rj, 1.0) : 0.0;
+        const double wi = si <= tau ? 0.0 : fma(-tau, ri, 1.0), wj = sj <= tau ? 0.0 : fma(-tau, rj, 1.0);
         if (i == j) {
           w[i] = wi;
           B[i * LD + i] = fma(-mii, wi, wi);

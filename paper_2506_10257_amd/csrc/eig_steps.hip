@@ -394,7 +394,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       const double sii = ld<TEAM>(as_global<double>(static_cast<const void*>(e.S + tid * (nb + 1))));
       const double m = ld<TEAM>(as_global<double>(static_cast<const void*>(e.C + tid * (nb + 1)))) - 1.0;
       const double di = fma(-m, sii, sii), si = sqrt_or_zero(di);
-      const double wi = si > tau ? 1.0 - tau * rcp_pos(si) : 0.0;
+      const double wi = si <= tau ? 0.0 : 1.0 - tau * rcp_pos(si);
       sd[tid] = sii;
       dg[tid] = di;
       sg[tid] = si;

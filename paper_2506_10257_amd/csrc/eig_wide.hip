@@ -627,8 +627,8 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
 
   // SVT weights and P = V diag(w) V^T (exactly symmetric), in storage precision.
   if (tid < n) {
-    const double sg = sqrt(fmax(Gp[pk(tid, tid)], 0.0));
-    w[tid] = sg > tau ? (sg - tau) / sg : 0.0;
+    const double g = Gp[pk(tid, tid)], sg = g <= 0.0 ? 0.0 : sqrt(g);
+    w[tid] = sg <= tau ? 0.0 : (sg - tau) / sg;  // (NaN where the Gram overflowed)
   }
   __syncthreads();
   const gptr<T> Pd = as_global<T>(d.P);
