@@ -54,6 +54,7 @@ k_eig(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
     pf_nXF2 = st->nXF2;
     pf_tau = st->tau;
   }
+  int shift = eig_shift(st->nXF2);  // (0 before the first control step)
   const bool warm = kd > 0;
   const int nfull = n * n;
 
@@ -128,8 +129,13 @@ k_eig(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
   }
   __syncthreads();
   if (!s_go) return;
+  if (kd == 0 && !d.warm) shift = eig_shift(scal[2]);
+  if (shift != 0) {
+    for (int idx = tid; idx < NMAX * LD; idx += NT) G0s[idx] = ldexp(G0s[idx], -2 * shift);
+    __syncthreads();
+  }
   EIG_MARK(0);
-  const double tau = s_tau;
+  const double tau = ldexp(s_tau, -shift);
   int sweeps = 0;
   const gptr<T> Pd = as_global<T>(d.P);
   const int cur = eig_core<T, NMAX, NT>(

@@ -298,6 +298,15 @@ __device__ inline double dot4(F&& term) {
   return (s0 + s1) + (s2 + s3);
 }
 
+// The eigensolve runs on A / 2^e (the Gram / 2^2e, tau / 2^e), whose projector is
+// the same: e = 0 unless ||X||_F^2 lies so far from 1 that squares of the Gram's
+// entries, which rotations and their tests form, would leave the range of a
+// double.  No FP32 input needs it (||X||_F^2 between 2^-298 and 2^286).
+__device__ inline int eig_shift(double nXF2) {
+  const int e = __builtin_amdgcn_frexp_exp(nXF2);  // 0 for 0 and infinity
+  return e >= -300 && e <= 300 ? 0 : __builtin_amdgcn_readfirstlane(max(-1000, min(1000, e)) / 2);
+}
+
 // Control step of an eigensolve launch, run by one thread after the
 // reduction has put the pass's scalars in scal (r2, sum|X|, sum X^2,
 // non-finite count).  At the first step it records the norms of X and fixes

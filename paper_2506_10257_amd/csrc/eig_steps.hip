@@ -293,6 +293,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
   const WideEig e(d);
   const int n = d.n, nb = d.nb, kd = st->iter;
   double pf_nXF2 = 0.0, pf_tau = 0.0;
+  const int shift = eig_shift(st->nXF2);
   // workgroup g of the solve's team; thread and wave of the whole team
   const int g = TEAM ? blockIdx.x : 0;
   const int teams = TEAM && !d.alone ? gridDim.x : 1;
@@ -326,6 +327,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
       if (idx < kScalars) {
         scal[idx] = sum;
       } else {
+        sum = ldexp(sum, -2 * shift);
         const int g = idx - kScalars, blk = g >> 4, el = g & 15;
         const int bj = packed_col(blk), bi = blk - bj * (bj + 1) / 2;
         const int i = 4 * bi + (el >> 2), j = 4 * bj + (el & 3);
@@ -374,7 +376,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     __syncthreads();
     if (!s_go) return;
   }
-  const double tau = s_tau;
+  const double tau = ldexp(s_tau, -shift);
   u = gw;
   product<TEAM, true>(u, nw, V, e.W, nb, put_sym(e.S));
   product<TEAM, true>(u, nw, V, V, nb, put(e.C));

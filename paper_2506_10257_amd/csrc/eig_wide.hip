@@ -156,6 +156,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
     pf_nXF2 = st->nXF2;
     pf_tau = st->tau;
   }
+  int shift = eig_shift(st->nXF2);  // (0 before the first control step)
 
   const bool warm = kd > 0 || handed;
   // (warm starts only: the cold start's rotations build all of V, and D
@@ -225,8 +226,13 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
   }
   __syncthreads();
   if (!s_go) return;
+  if (kd == 0 && !handed && !d.warm) shift = eig_shift(scal[2]);
+  if (shift != 0) {
+    for (int idx = tid; idx < NPK; idx += NT) Gp[idx] = ldexp(Gp[idx], -2 * shift);
+    __syncthreads();
+  }
   EIG_MARK(0);
-  const double tau = s_tau;
+  const double tau = ldexp(s_tau, -shift);
 
   if (warm) {
     // W = G V (every 16 x 16 block) into the scratch buffer, then the upper

@@ -1,6 +1,7 @@
-"""Finite FP64 inputs whose Gram overflows (sums of squares above 1.8e308): the
+"""FP64 inputs far from one.  Those whose Gram overflows (sums of squares above 1.8e308): the
 solve says RPCA_ERR_NONFINITE, by every eigensolver and entry point, instead of
-dropping the infinite eigenvalues."""
+dropping the infinite eigenvalues; all others give what the same input near one
+gives."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,17 @@ def test_an_overflowing_gram_is_an_error(n):
         Z[n // 2, 0, 3] = 1e300
         with pytest.raises(RuntimeError, match=NONFINITE):
             rp.solve(X, tol=1e-6, maxit=20, **{name: Z})
+
+
+@pytest.mark.parametrize("scale", [2.0**-340, 2.0**-260, 2.0**255, 2.0**330, 2.0**495])
+@pytest.mark.parametrize("n", [1, 10, 20, 32, 33, 64, 65, 100, 113, 128])
+def test_powers_of_two_change_no_bit(n, scale):
+    """X and its multiple by a power of two: the same iterates, scaled, as long as
+    the sums of squares themselves stay in range."""
+    import torch
+    X = _window(n)
+    X[n // 2, 0, ::7] += 3.0
+    want = rp.solve(X, tol=0.0, maxit=8)
+    for got in (rp.solve(X * scale, tol=0.0, maxit=8), rp.solve_many([X * scale, X * scale], tol=0.0, maxit=8)[1]):
+        assert got.iterations == 8
+        assert torch.equal(got.L, want.L * scale) and torch.equal(got.S, want.S * scale)
