@@ -369,7 +369,9 @@ int rpca_server_step(rpca_server* s, rpca_completion* out, int32_t capacity, int
 int rpca_server_pending(rpca_server* s, int32_t* queued, int32_t* active, size_t* bytes_in_use);
 /* Largest admitted footprint seen so far (bytes). */
 size_t rpca_server_peak_bytes(rpca_server* s);
-/* Admission footprint of one request: workspace + M, L and S. 0 if unsupported. */
+/* Admission footprint of one request: workspace + M, L and S. 0 if unsupported.
+ * Above 64 frames the workspace counts without the matrices of the eigensolver's
+ * simultaneous steps (0.6 to 2 MB, part of rpca_footprint_bytes). */
 size_t rpca_server_request_bytes(int64_t m, int64_t n, int32_t dtype);
 /* Wait for device work, free every workspace and drop queued requests. */
 void rpca_server_destroy(rpca_server* s);

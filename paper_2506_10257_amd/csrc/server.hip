@@ -421,7 +421,9 @@ extern "C" {
 
 size_t rpca_server_request_bytes(int64_t m, int64_t n, int32_t dtype) {
   const size_t ws = rpca_footprint_bytes(m, n, dtype);
-  return ws == 0 ? 0 : ws + io_bytes(m, n, dtype);
+  if (ws == 0) return 0;
+  const int nb = static_cast<int>((n + 15) / 16 * 16);  // the tile kernel's class
+  return ws - steps_bytes(static_cast<int>(n), nb) + io_bytes(m, n, dtype);
 }
 
 rpca_server* rpca_server_create(int32_t dtype, int32_t gram_mode, size_t hbm_budget,
