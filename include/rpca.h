@@ -33,7 +33,17 @@
  * their host-side outputs then.
  *
  * Threads: calls are thread-safe; calls on different streams run
- * independently.
+ * independently, and their results do not depend on what runs beside them.  They
+ * share the device, and so do launches of the caller's own: a single solve of up
+ * to 32 frames (FP64: 20) and up to 1000 iterations may run as one launch that
+ * holds its CUs until it ends, all of them for the larger images.  It is used
+ * for a large image only while no other call of the process is under way on the
+ * device, but launches that come meanwhile, from any stream, wait for its end
+ * (16 to 18 ms for 500 iterations of 512 x 512 x 20).  Where other work holds a CU
+ * for more than 5 ms, the launch gives up and the solve runs in many small ones;
+ * after that the next 1, 2, 4, ... 64 solves run that way at once.  With kernel
+ * timing on, or as one of several problems of rpca_solve_many, or in a server, a
+ * solve always runs in small launches.
  */
 #ifndef RPCA_MI355X_H
 #define RPCA_MI355X_H

@@ -27,11 +27,13 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <utility>
 #include <vector>
 
 #include "rpca.h"
 #include "common.h"
+#include "device_use.h"
 #include "engine.h"
 #include "launch.h"
 
@@ -103,6 +105,11 @@ void ev_end(hipStream_t s) {
 namespace {
 std::once_flag g_pool_once[64];
 }  // namespace
+
+DeviceUse& device_use(int dev) {
+  static DeviceUse use[64];
+  return use[dev];
+}
 
 void setup_pool(int dev) {
   if (dev < 0 || dev >= 64) return;
@@ -811,17 +818,16 @@ int lease_lanes(int dev, int nlanes, int count, LaneLease& lease, Lanes& view) {
 
 // Whole-solve kernel (resident_impl.h): chosen for a single solve on the
 // register kernel with one tile per slot whose tiles fit the device's CUs, two
-// per workgroup, or four for FP32 windows of up to 20 frames: that is what fits
+// per workgroup, or four for FP32 windows of up to 20 frames: more do not fit
 // the registers.  Iteration in the kernel / launched (us): 512 x 512 x 20 FP32
 // 36 / 49, 128 x 128 x 20 FP64 25 / 39; 60 of 338 x 260 x 20 FP32 1.6 / 3.0 ms.  With kernel
-// timing on, and while another such solve runs on the device (the second one's
-// workgroups would wait for the first one's CUs), the launches are used.
-constexpr int kResidentMaxIt = 20000;  // bounds one launch (about half a second)
-constexpr int kNotRun = INT32_MIN;     // run_resident: take the launched path
-std::mutex g_resident_mu[64];          // one such solve at a time per device
+// timing on, beside other calls (device_use.h) and above kResidentMaxIt iterations, the
+// launches are used.
+constexpr int kResidentMaxIt = 1000;  // one launch holds the device for 45 ms at most
+constexpr int kNotRun = INT32_MIN;    // run_resident: take the launched path
 
 struct ResidentPlan {
-  int nb = 0, threads = 0, grid = 0, tpw = 0, ushift = 0;
+  int nb = 0, threads = 0, grid = 0, tpw = 0, ushift = 0, cus = 0;
 };
 
 bool resident_plan(const SolveRec& r, int dtype, int cus, ResidentPlan& p) {
@@ -841,44 +847,39 @@ bool resident_plan(const SolveRec& r, int dtype, int cus, ResidentPlan& p) {
   }
   if (p.grid == 0) return false;
   p.threads = p.tpw == 4 ? 1024 : 512;
+  p.cus = cus;
   p.ushift = 0;
   while ((1 << p.ushift) < p.grid) ++p.ushift;
   return true;
 }
 
-int run_resident(rpca_problem& prob, const SolveRec& rec, int dtype, int dev, hipStream_t user) {
+bool could_be_whole(const SolveRec& rec, int dtype, int dev, ResidentPlan& rp) {
   static std::atomic<int> cus[64];
-  if (dev < 0 || dev >= 64) return kNotRun;
+  if (dev < 0 || dev >= 64) return false;
   int ncu = cus[dev].load(std::memory_order_relaxed);
   if (ncu == 0) {
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
       (void)hipGetLastError();
-      return kNotRun;
+      return false;
     }
     cus[dev].store(ncu, std::memory_order_relaxed);
   }
-  ResidentPlan rp;
-  if (!resident_plan(rec, dtype, ncu, rp)) return kNotRun;
-  // A second such grid would wait for CUs that the first one holds.
-  std::unique_lock<std::mutex> lk(g_resident_mu[dev], std::try_to_lock);
-  if (!lk.owns_lock()) return kNotRun;
+  return resident_plan(rec, dtype, ncu, rp);
+}
 
+// The inputs are ready (the caller's stream was synchronised).
+int run_resident(rpca_problem& prob, const SolveRec& rec, const ResidentPlan& rp, int dtype, int dev) {
   LaneLease lease;
   Lanes L;
   int rc = lease_lanes(dev, 1, 2, lease, L);
   if (rc != RPCA_OK) return rc;
   hipStream_t s = L.s[0];
-  hipError_t e = hipStreamSynchronize(user);  // inputs are produced on the caller's stream
-  if (e != hipSuccess) {
-    set_error("hipStreamSynchronize(caller stream)", e);
-    return RPCA_ERR_DEVICE;
-  }
   // state and the lost flag first (read back together), then the words
   const size_t head = al256(sizeof(SolveState) + sizeof(uint64_t));
   const size_t nent = static_cast<size_t>(pstride_for(rec.n));
   const size_t parts = al256(nent * rp.grid * 2 * sizeof(uint64_t)), sums = al256(nent * 2 * sizeof(uint64_t));
   char* mem = nullptr;
-  e = hipMallocAsync(reinterpret_cast<void**>(&mem), head + parts + sums, s);
+  hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&mem), head + parts + sums, s);
   if (e != hipSuccess || mem == nullptr) {
     set_error("hipMallocAsync(exchange)", e);
     (void)hipGetLastError();
@@ -969,9 +970,24 @@ int run_pass(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream
   }
   setup_pool(dev);
 
-  if (count == 1 && !prof) {
-    const int rrc = run_resident(probs[0], recs[0], dtype, dev, user);
-    if (rrc != kNotRun) return rrc;
+  std::optional<OtherCall> other;
+  std::optional<SingleCall> single;
+  ResidentPlan rp;
+  if (count == 1 && !prof && could_be_whole(recs[0], dtype, dev, rp)) {
+    // inputs are produced on the caller's stream
+    const hipError_t e = hipStreamSynchronize(user);
+    if (e != hipSuccess) {
+      set_error("hipStreamSynchronize(caller stream)", e);
+      return RPCA_ERR_DEVICE;
+    }
+    single.emplace(dev, rp.grid, rp.cus);
+    if (single->whole()) {
+      const int rrc = run_resident(probs[0], recs[0], rp, dtype, dev);
+      if (rrc != kNotRun) return rrc;
+      if (t_limits.arrive_ticks == RunLimits{}.arrive_ticks) single->gave_up();  // (not where a test made it)
+    }
+  } else {
+    other.emplace(dev);
   }
 
   const bool use_graph = !prof && !graphs_disabled();

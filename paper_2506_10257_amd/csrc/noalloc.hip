@@ -26,6 +26,7 @@
 
 #include "rpca.h"
 #include "common.h"
+#include "device_use.h"
 #include "engine.h"
 #include "launch.h"
 
@@ -104,6 +105,7 @@ int solve_noalloc(const rpca_problem& p, int dtype, hipStream_t stream, int32_t*
     set_error("hipGetDevice", e);
     return RPCA_ERR_DEVICE;
   }
+  const OtherCall other(dev);
   std::lock_guard<std::mutex> lk(g_dev_mu[dev]);
   char* base = scratch_address(dev);
   if (base == nullptr) return RPCA_ERR_DEVICE;

@@ -22,6 +22,7 @@
 
 #include "rpca.h"
 #include "common.h"
+#include "device_use.h"
 #include "engine.h"
 
 namespace rpca {
@@ -331,6 +332,9 @@ int grid_for(int64_t count) {
 // results to host memory `out` (stream-ordered, then synchronised).
 template <typename V, typename Launch>
 int reduce_to_host(hipStream_t s, int grid, int len, V* out, Launch&& launch) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) (void)hipGetLastError();
+  const OtherCall other(dev);
   V* buf = nullptr;
   const size_t bytes = sizeof(V) * (static_cast<size_t>(grid) + 1) * len;
   hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&buf), bytes, s);

@@ -37,10 +37,12 @@
 #include <deque>
 #include <mutex>
 #include <new>
+#include <optional>
 #include <vector>
 
 #include "rpca.h"
 #include "common.h"
+#include "device_use.h"
 #include "engine.h"
 #include "launch.h"
 
@@ -70,6 +72,8 @@ struct rpca_server {
   int max_active = 1, quantum = 1;
   bool simulate = false;
   bool broken = false;
+  int dev = 0;
+  std::optional<rpca::OtherCall> busy;  // while requests are active, also between steps
   hipStream_t user = nullptr;
   std::deque<rpca::Req*> queue;
   std::vector<rpca::Req*> active;
@@ -310,10 +314,14 @@ int step_device(rpca_server* s) {
   std::vector<Req*> fresh;
   admit(s, fresh);
   if (!fresh.empty()) {
+    if (!s->busy) s->busy.emplace(s->dev);
     const int rc = start_admitted(s, fresh);
     if (rc != RPCA_OK) return rc;
   }
-  if (s->active.empty()) return RPCA_OK;
+  if (s->active.empty()) {
+    s->busy.reset();
+    return RPCA_OK;
+  }
 
   // 3. one quantum of iterations for every active solve
   if (!s->plan_valid) {
@@ -407,7 +415,9 @@ int step_device(rpca_server* s) {
     r->rec.alone = 1;
     s->plan_valid = false;
   }
-  return init_stage(s, again);
+  const int rca = init_stage(s, again);
+  if (s->active.empty()) s->busy.reset();
+  return rca;
 }
 
 #undef SV
@@ -451,6 +461,7 @@ rpca_server* rpca_server_create(int32_t dtype, int32_t gram_mode, size_t hbm_bud
       return nullptr;
     }
     setup_pool(dev);
+    s->dev = dev;
   }
   return s;
 }
