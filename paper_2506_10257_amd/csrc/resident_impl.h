@@ -76,7 +76,7 @@ __device__ inline bool ll_wait(const uint64_t* cell, uint32_t seq, int64_t ticks
 // instruction beside the FMAs.  With scalar loads, as in k_stream, the scalar
 // cache would have to be invalidated every iteration; through v_readlane the
 // update took 10.4 us at 512 x 512 x 20.  (s_nop: two wait states between a
-// write of p and its DPP use.)
+// write of p and its DPP use; the sums are written before the last read of p and a.)
 template <int BLK, typename T>
 __device__ inline void fma_row(T* l, T p, T a) {
   static_assert(BLK == 8 || BLK == 10, "columns per row of P");
@@ -91,7 +91,7 @@ __device__ inline void fma_row(T* l, T p, T a) {
           "v_fmac_f32_dpp %5, %8, %9 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f32_dpp %6, %8, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f32_dpp %7, %8, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
-          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7])
+          : "+&v"(l[0]), "+&v"(l[1]), "+&v"(l[2]), "+&v"(l[3]), "+&v"(l[4]), "+&v"(l[5]), "+&v"(l[6]), "+&v"(l[7])
           : "v"(p), "v"(a));
     } else {
       asm("s_nop 1\n\t"
@@ -105,7 +105,7 @@ __device__ inline void fma_row(T* l, T p, T a) {
           "v_fmac_f32_dpp %7, %10, %11 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f32_dpp %8, %10, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f32_dpp %9, %10, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
-          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7]), "+v"(l[8]), "+v"(l[9])
+          : "+&v"(l[0]), "+&v"(l[1]), "+&v"(l[2]), "+&v"(l[3]), "+&v"(l[4]), "+&v"(l[5]), "+&v"(l[6]), "+&v"(l[7]), "+&v"(l[8]), "+&v"(l[9])
           : "v"(p), "v"(a));
     }
   } else {
@@ -119,7 +119,7 @@ __device__ inline void fma_row(T* l, T p, T a) {
           "v_fmac_f64_dpp %5, %8, %9 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f64_dpp %6, %8, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f64_dpp %7, %8, %9 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
-          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7])
+          : "+&v"(l[0]), "+&v"(l[1]), "+&v"(l[2]), "+&v"(l[3]), "+&v"(l[4]), "+&v"(l[5]), "+&v"(l[6]), "+&v"(l[7])
           : "v"(p), "v"(a));
     } else {
       asm("s_nop 1\n\t"
@@ -133,7 +133,7 @@ __device__ inline void fma_row(T* l, T p, T a) {
           "v_fmac_f64_dpp %7, %10, %11 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f64_dpp %8, %10, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
           "v_fmac_f64_dpp %9, %10, %11 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
-          : "+v"(l[0]), "+v"(l[1]), "+v"(l[2]), "+v"(l[3]), "+v"(l[4]), "+v"(l[5]), "+v"(l[6]), "+v"(l[7]), "+v"(l[8]), "+v"(l[9])
+          : "+&v"(l[0]), "+&v"(l[1]), "+&v"(l[2]), "+&v"(l[3]), "+&v"(l[4]), "+&v"(l[5]), "+&v"(l[6]), "+&v"(l[7]), "+&v"(l[8]), "+&v"(l[9])
           : "v"(p), "v"(a));
     }
   }
