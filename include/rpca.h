@@ -238,6 +238,8 @@ int rpca_inject_wait(double seconds);
 #define RPCA_RUN_WHOLE      1  /* in one launch, all iterations in the kernel */
 #define RPCA_RUN_WHOLE_LOST 2  /* ... that gave up a wait: run again by launches */
 #define RPCA_RUN_TEAM_LOST  4  /* above 64 frames: an eigensolver team gave one up */
+#define RPCA_RUN_SWEEPS     8  /* above 64 frames: the last eigensolve of a problem
+                                  ended in sweeps (its steps did not converge) */
 int rpca_last_run(void);
 
 /*

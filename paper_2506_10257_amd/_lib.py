@@ -33,6 +33,7 @@ RPCA_KNOB_REG_TILES = 4
 RPCA_RUN_WHOLE = 1
 RPCA_RUN_WHOLE_LOST = 2
 RPCA_RUN_TEAM_LOST = 4
+RPCA_RUN_SWEEPS = 8
 RPCA_SERVER_SIMULATE = 1
 RPCA_SERVER_STAGE_INIT = 1
 RPCA_NOALLOC_MAX_BYTES = 192 << 20

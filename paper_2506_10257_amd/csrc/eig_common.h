@@ -49,7 +49,7 @@ struct OrthGoal<float> {
 // Column j of packed upper index idx = j (j + 1) / 2 + i, i <= j (idx < 2^22:
 // the float square root is exact enough to be off by at most one).
 __device__ inline int packed_col(int idx) {
-  int j = static_cast<int>((__builtin_sqrtf(8.0f * static_cast<float>(idx) + 1.0f) - 1.0f) * 0.5f);
+  int j = static_cast<int>(fmaf(__builtin_sqrtf(fmaf(8.0f, static_cast<float>(idx), 1.0f)), 0.5f, -0.5f));
   if (j * (j + 1) / 2 > idx) --j;
   else if ((j + 1) * (j + 2) / 2 <= idx) ++j;
   return j;
@@ -154,8 +154,7 @@ __device__ inline void make_rotation(double gpp, double gqq, double gpq, double&
   if (off_diag_large<T>(gpq, gpp, gqq)) {
     const double d = gqq - gpp;
     const double h2 = fma(d, d, 4.0 * gpq * gpq);   // > 0 since gpq != 0
-    const double h = h2 * rsqrt_pos(h2);
-    double t = 2.0 * gpq * rcp_pos(fabs(d) + h);
+    double t = 2.0 * gpq * rcp_pos(fma(h2, rsqrt_pos(h2), fabs(d)));
     if (d < 0.0) t = -t;
     c = rsqrt_pos(fma(t, t, 1.0));
     s = t * c;
@@ -214,7 +213,7 @@ __device__ inline PairTerms pair_terms(double e, double di, double dj, double si
   if (ki || kj || !safe || smax > 0.125 * tau) {
     const double h2 = fma(g, g, 4.0 * e * e);
     if (h2 > kTiny2) {
-      const double t = 2.0 * e * rcp_pos(ag + h2 * rsqrt_pos(h2));
+      const double t = 2.0 * e * rcp_pos(fma(h2, rsqrt_pos(h2), ag));
       o.t = fmin(fmax(g < 0.0 ? -t : t, -kTangentMax), kTangentMax);
     }
   }

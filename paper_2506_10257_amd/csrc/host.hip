@@ -1107,6 +1107,7 @@ int run_pass(rpca_problem* probs, int count, int dtype, int gram_mode, hipStream
       const SolveState& st = L.pinned[0][i];
       recs[i].st = st;
       if (st.status == kLostTeam) g_last_run |= RPCA_RUN_TEAM_LOST;
+      else if (recs[i].n > kEigMaxN && st.sweeps > 0) g_last_run |= RPCA_RUN_SWEEPS;
       probs[i].iterations = st.iter;
       probs[i].status = st.status;
       probs[i].residual = st.resid;
