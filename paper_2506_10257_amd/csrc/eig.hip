@@ -108,7 +108,7 @@ k_eig(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids) {
         const int bj = packed_col(blk);
         const int bi = blk - bj * (bj + 1) / 2;
         const int i = 4 * bi + (e >> 2), j = 4 * bj + (e & 3);
-        if (i < n && j < n) {
+        if (i <= j && j < n) {  // (split BF16: the other halves of the diagonal blocks differ)
           G0s[i * LD + j] = sum;
           G0s[j * LD + i] = sum;
         }
