@@ -318,10 +318,7 @@ int step_device(rpca_server* s) {
     const int rc = start_admitted(s, fresh);
     if (rc != RPCA_OK) return rc;
   }
-  if (s->active.empty()) {
-    s->busy.reset();
-    return RPCA_OK;
-  }
+  if (s->active.empty()) return RPCA_OK;
 
   // 3. one quantum of iterations for every active solve
   if (!s->plan_valid) {
@@ -415,9 +412,7 @@ int step_device(rpca_server* s) {
     r->rec.alone = 1;
     s->plan_valid = false;
   }
-  const int rca = init_stage(s, again);
-  if (s->active.empty()) s->busy.reset();
-  return rca;
+  return init_stage(s, again);
 }
 
 #undef SV
@@ -516,6 +511,7 @@ int rpca_server_step(rpca_server* s, rpca_completion* out, int32_t capacity, int
   if (s->broken) return RPCA_ERR_DEVICE;
   const int rc = s->simulate ? step_simulated(s) : step_device(s);
   if (rc == RPCA_ERR_DEVICE) s->broken = true;
+  if (s->active.empty() || s->broken) s->busy.reset();
   int k = 0;
   while (k < capacity && !s->ready.empty()) {
     out[k++] = s->ready.front();

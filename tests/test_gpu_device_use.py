@@ -43,6 +43,19 @@ def test_whole_solves_beside_a_server():
     assert runs[0][0] and not runs[-1][0]
 
 
+def test_a_server_whose_set_up_failed_holds_nobody_back():
+    device()
+    large = _window(262144, 20)
+    srv = rp.Server(dtype=rp.RPCA_F32, hbm_budget=1 << 30, max_active=2, quantum=2)
+    assert srv.inject_failure(rp.RPCA_ERR_DEVICE) == rp.RPCA_OK
+    srv.submit(_window(5000, 40), 1, tol=0.0, maxit=6)
+    with pytest.raises(RuntimeError):  # a device error: every later step fails too
+        for _ in range(3):
+            srv.step()
+    rp.solve(large, tol=0.0, maxit=3)
+    assert _ran() == _lib.RPCA_RUN_WHOLE
+
+
 def test_more_than_a_thousand_iterations_go_by_launches():
     import torch
     device()
