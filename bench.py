@@ -3,8 +3,8 @@
 Workload: the seeded 512x512-pixel x 20-frame ultrasound window (Casorati
 262144 x 20), FP32, lambda = 1/512, tol = 1e-6, maxit = 1000.  One step is
 one complete solve (init pass, every iteration, finalize) with the input
-already resident in HBM, on the production path (graph-captured iteration
-chunks).
+already resident in HBM, on the production path (one whole-solve launch, or
+graph-captured iteration chunks).
 
 value = sum over timed steps of m * n * iterations / wall time of the steps.
 
@@ -12,9 +12,13 @@ The JSON line also carries
   roofline     : the fused update kernel's algorithmic bytes per launch over
                  its mean launch time (a HIP start/stop event pair that each
                  launch records on its own stream from its dispatch packet,
-                 over a repeat of the timed steps) against
+                 over a repeat of the timed steps by launches) against
                  the 8 TB/s HBM peak, and the HBM bytes per launch measured
-                 with rocprofv3 counters (profiles/);
+                 with rocprofv3 counters (profiles/).  The timed steps
+                 themselves run in one launch each where the window fits the
+                 register files (timed_steps_ran): their iterates then move
+                 no bytes, and the per-iteration figures are those that a
+                 launched iteration of the same speed would reach;
   cpu_baseline : the FP64 CPU oracle timed on a bounded number of iterations
                  of the same window on this host;
   latency      : p50 / p99 of the per-solve wall time.
@@ -882,6 +886,7 @@ def main():
     import torch
 
     import paper_2506_10257_amd as rp
+    from paper_2506_10257_amd import _lib
     from synth import window_512x512x20
 
     dev = torch.device("cuda:0")
@@ -897,7 +902,7 @@ def main():
         rp.solve(M, lam=lam, tol=tol, maxit=maxit)
     torch.cuda.synchronize()
 
-    # Timed region: the production path (graph-captured iteration chunks).
+    # Timed region: the production path.
     times, iters = [], []
     torch.cuda.synchronize()
     t_start = time.perf_counter()
@@ -909,6 +914,7 @@ def main():
         iters.append(r.iterations)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t_start
+    whole = bool(_lib.load().rpca_last_run() & _lib.RPCA_RUN_WHOLE)
 
     # Kernel timing: the same steps again, every launch recording a HIP
     # start/stop event pair of its own on the launching stream (direct
@@ -972,7 +978,10 @@ def main():
                      "kernel": kname,
                      "bytes_per_launch": bytes_per_launch, "mean_launch_us": upd_ms * 1e3,
                      "launches": prof["update_launches"],
-                     "measured_on": "the same steps repeated, each launch recording its own HIP "
+                     # the kernels above are those of the launched path; the
+                     # per-iteration figures count its five words per entry
+                     "timed_steps_ran": "one whole-solve launch per step" if whole else "launched iterations",
+                     "measured_on": "the same steps repeated by launches, each recording its own HIP "
                                     "start/stop event pair"},
         "phase_ms_per_solve": {k: prof[k] / max(prof["solves"], 1)
                                for k in ("init_ms", "eig_ms", "update_ms", "finalize_ms")},

@@ -254,6 +254,12 @@ int rpca_last_run(void);
  * or value (the knob is then unchanged).  rpca_tune_get returns the current
  * value, or RPCA_ERR_ARG.  The eigensolver sizes change only speed: every
  * variant computes the same arithmetic in the same order.
+ *
+ * The knobs choose between launches.  A single solve in one launch (see
+ * "Threads" at the top) has sizes of its own, which RPCA_KNOB_EIG_THREADS does
+ * not change; where RPCA_KNOB_STREAM_KERNEL is 1 for its class, or
+ * RPCA_KNOB_REG_TILES above 1 applies to it, it goes by launches too, so that
+ * its bits are those of the same problem in a batch.
  */
 #define RPCA_KNOB_EIG_THREADS 1
 /*   RPCA_KNOB_STREAM_KERNEL streaming kernel of one FP32 frame class (`cls` =
@@ -400,7 +406,9 @@ int rpca_server_inject_failure(rpca_server* s, int32_t stage, int32_t code);
  *
  * rpca_autotune runs short solves (tol = 0, a dozen iterations) of synthetic
  * windows through the library with kernel timing on, for each variant of
- * each knob, and keeps the fastest:
+ * each knob, and keeps the fastest launch (a solve in one launch is not timed:
+ * where the tile kernel wins a class of 16 to 32 frames, or several tiles per
+ * workgroup do, single solves of that class lose it):
  *   - RPCA_KNOB_EIG_THREADS per eigensolver class, on a 16384 x cls window;
  *   - RPCA_KNOB_STREAM_KERNEL per FP32 register class of 16 frames or more,
  *     on a `rows` x cls window (rows >= 256; e.g. 262144 for 512 x 512

@@ -11,7 +11,7 @@ namespace eigk {
 constexpr double kTiny2 = 1.0e-300;
 constexpr int kMaxSweeps = 40;
 
-// Simultaneous rotation steps (see eig.hip).
+// Simultaneous rotation steps (see eig_core.h).
 constexpr int kMaxSteps = 12;          // per launch; then sweeps only
 constexpr int kMaxPasses = 100;        // steps and sweeps together
 constexpr float kOrthMax = 0.25f;      // largest |V^T V - I| entry that a step starts from

@@ -1,7 +1,7 @@
 // Warm-started eigensolve of windows of 65 to 144 frames by simultaneous
 // rotation steps, by a team of workgroups per solve.
 //
-// The method is that of the simultaneous steps in eig.hip: all pairs of the
+// The method is that of the simultaneous steps in eig_core.h: all pairs of the
 // nearly diagonal G~ = V^T G V are rotated at once through matrix products, and
 // P = V Z V^T with Z the first-order expansion of the thresholding function at
 // the diagonal of G~.  Here the matrices (up to 166 KB each) stay in the
@@ -30,7 +30,8 @@
 // of the widest phase: then a phase is one block's latency and the meeting after
 // it, 6 to 8 us, and a launch 100 (125) us.  A launch of several solves divides
 // kTeamGroups workgroups between them.  The blocks are computed alike however
-// many workgroups there are, so the results have the same bits.
+// many workgroups there are, and products and sums are fused only where the code
+// says so (the build's -ffp-contract=off), so the results have the same bits.
 //
 // A workgroup waits for its team at every meeting, for a bounded time (launch.h);
 // then it gives up and the others follow at this meeting or a later one.  The

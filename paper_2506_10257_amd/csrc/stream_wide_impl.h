@@ -117,8 +117,9 @@ __device__ inline void split_any(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
 
 // Wavefronts per SIMD that the registers are held to: two workgroups per CU
 // where that needs no spills, so that one's loads and barriers are hidden
-// behind the other's products.  (FP32 at 64 frames fits too, with L over the A
-// tile, but without its next tile's loads in flight: 3 to 7% slower.)
+// behind the other's products.  (FP32 at 64 frames is not held to it: 122
+// registers and 41.7 KB of LDS as it is.  With L over the A tile and without its
+// next tile's loads in flight it was 3 to 7% slower.)
 template <typename T>
 __host__ __device__ constexpr int waves_per_simd(int nb, int prec) {
   return sizeof(T) == 4 && nb <= 48 ? 4 : 2;
