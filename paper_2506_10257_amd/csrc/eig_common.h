@@ -20,9 +20,10 @@ constexpr double kTangentMax = 0.5;    // tangents are clipped here
 constexpr float kColdTangent = 0.25f;  // first launch: steps only once every tangent is below
 constexpr float kWideFourth = 0.02f;   // wide solves: above this tangent, U to fourth order
 
-// Bound on the second-order error of an entry of P: for FP32 solves below the
-// rounding of P's own entries (and that of the diagonal Z this replaces, whose
-// off-diagonals were left out up to 1e-8 sigma_i sigma_j: 5e-9), for FP64
+// Bound on the second-order error of an entry of P: for FP32 solves half the
+// rounding of P's own entries (over the iterations of 20-frame windows the error
+// itself stays below 2e-9, that of the diagonal Z this replaces, whose
+// off-diagonals were left out up to 1e-8 sigma_i sigma_j, below 5e-9), for FP64
 // solves at the rounding of the products.
 template <typename T>
 struct PTarget;
@@ -32,7 +33,7 @@ struct PTarget<double> {
 };
 template <>
 struct PTarget<float> {
-  static constexpr float value = 5.0e-9f;
+  static constexpr float value = 3.0e-8f;
 };
 // Entries of |V^T V - I| below which V counts as orthogonal.
 template <typename T>
@@ -171,22 +172,31 @@ __device__ inline void make_rotation(double gpp, double gqq, double gpq, double&
 // factors mz, kappa of its error bound, the clipped tangent t of the rotation,
 // and whether the sweeps would rotate the pair.
 //
-// kappa is the rotation's tangent |e| / |di - dj|; for two kept values, where
-// w is smooth, |e| / min(di, dj) will do when that is smaller, and for two
-// dropped values, where w vanishes, 0.  Both hold only while the pair's values
-// stay on their side of the threshold tau^2 whatever the off-diagonals do: by
-// Gershgorin when n |e| is at most their distance from it (if that holds for
-// every pair of a row, the row's radius is within the distance).  Pairs far
-// below the threshold that are safe in this sense are not rotated at all: they
-// are the rounding noise of rank-deficient windows, and P never sees them.
+// The second-order terms of P are products e_ij e_jk of two pairs with a second
+// divided difference of w, which is a difference of two first ones (slopes of w,
+// w'(d) where two indices agree) over a gap.  mz is |e| times the largest slope
+// that the pair can bring: w[di, dj], w' = tau / (2 d^1.5) of a kept value, and
+// w' = 1/(2 tau^2) at the threshold where a value may lie on either side of it
+// (w[di, dj] alone is nearly zero for a value just above the threshold, and a
+// window with one column there was taken for converged, with P = 0).  kappa is
+// |e| over the gap: |di - dj|; for two kept values, where w is smooth, min(di, dj)
+// when that is larger; for two dropped values, whose own term vanishes but which
+// pass on what a kept value couples to one of them, the distance of the larger
+// from the threshold.  The last two hold only while the pair's values stay on
+// their side of the threshold tau^2 whatever the off-diagonals do: by Gershgorin
+// when n |e| is at most their distance from it (if that holds for every pair of a
+// row, the row's radius is within the distance).  Pairs far below the threshold
+// that are safe in this sense are not rotated at all: they are the rounding noise
+// of rank-deficient windows.
 struct PairTerms {
   double z, t;
   float mz, kappa;
   int rotate;
 };
+// ri, rj: 1/si and 1/sj (0 for a value of 0).
 template <typename T>
-__device__ inline PairTerms pair_terms(double e, double di, double dj, double si, double sj,
-                                       double wi, double wj, double tau, int n) {
+__device__ inline PairTerms pair_terms(double e, double di, double dj, double si, double sj, double ri,
+                                       double rj, double wi, double wj, double tau, int n) {
   PairTerms o;
   const double g = dj - di, ag = fabs(g), ae = fabs(e), tau2 = tau * tau;
   const bool ki = si > tau, kj = sj > tau;
@@ -198,18 +208,24 @@ __device__ inline PairTerms pair_terms(double e, double di, double dj, double si
   o.mz = 0.0f;
   o.kappa = 0.0f;
   if (ae == 0.0) return o;
-  double den = ag;  // kappa = ae / den
-  if (ki && kj) {
-    if (safe) den = fmax(ag, fmin(di, dj));
-    o.z = e * rcp_pos(si * sj) * (tau * rcp_pos(si + sj));
-    o.mz = fabsf(static_cast<float>(o.z));
-  } else if (ki || kj) {
-    o.z = e * ((ki ? wi : wj) * rcp_pos(ag));  // one above, one not: g != 0
-    o.mz = fabsf(static_cast<float>(o.z));
-  } else if (!safe) {
-    o.mz = static_cast<float>(ae * 0.5 * rcp_pos(tau2));  // the slope of w at the threshold
+  // (the bound's factors from the hardware's estimates of the reciprocals)
+  double q, mz = 0.0;  // 1 / gap, |e| times the largest slope
+  if (ki != kj) {
+    q = rcp_pos(ag);  // one above, one not: g != 0
+    const double rk = ki ? ri : rj;
+    o.z = e * ((ki ? wi : wj) * q);
+    mz = 0.5 * (tau * rk) * (ae * rk * rk);
+  } else if (ki) {
+    const double rm = fmax(ri, rj);
+    o.z = e * (ri * rj) * (tau * rcp_pos(si + sj));
+    mz = 0.5 * (tau * rm) * (ae * rm * rm);
+    q = __builtin_amdgcn_rcp(safe ? fmax(ag, fmin(di, dj)) : ag);
+  } else {
+    q = __builtin_amdgcn_rcp(safe ? tau2 - fmax(di, dj) : ag);
   }
-  if (ki || kj || !safe) o.kappa = den > 0.0 ? static_cast<float>(ae * rcp_pos(den)) : INFINITY;
+  if (!safe) mz = 0.5 * ae * __builtin_amdgcn_rcp(tau2);  // no slope is larger
+  o.mz = fmaxf(fabsf(static_cast<float>(o.z)), static_cast<float>(mz));
+  o.kappa = static_cast<float>(ae * q);  // (infinite for equal values that are not safe)
   if (ki || kj || !safe || smax > 0.125 * tau) {
     const double h2 = fma(g, g, 4.0 * e * e);
     if (h2 > kTiny2) {
@@ -244,8 +260,8 @@ __device__ inline void wave_max_to(float x, unsigned* cell) {
   if ((threadIdx.x & 63) == 0 && a != 0u) atomicMax(cell, a);
 }
 
-// sqrt(d), or 0 for d <= 0 (the rounding of a zero eigenvalue); NaN for infinity.
-__device__ inline double sqrt_or_zero(double d) { return d <= kTiny2 ? 0.0 : d * rsqrt_pos(d); }
+// 1/sqrt(d), or 0 for d <= 0 (the rounding of a zero eigenvalue); NaN for infinity.
+__device__ inline double rsqrt_or_zero(double d) { return d <= kTiny2 ? 0.0 : rsqrt_pos(d); }
 
 // View of a wide solve's workspace (see common.h).  cls is the class of the
 // Jacobi kernel, whose scratch comes first.

@@ -35,9 +35,10 @@
 //      w[,] of w).  It needs no gaps inside the kept or the dropped part of the
 //      spectrum, and its error is second order, so step 2 stops one step or
 //      sweep earlier than for a diagonal Z.  The second-order term is bounded
-//      by n max(|Z_ij|, |M_ij|) max(kappa_ij, |M_ij|), kappa in essence the
-//      pair's tangent (pair_terms); step 2 ends when that is below PTarget (or
-//      when no pair needs a rotation).
+//      by n max(mz_ij, |M_ij|) max(kappa_ij, |M_ij|), with mz the pair's
+//      off-diagonal times the largest slope of w it can bring and kappa in
+//      essence the pair's tangent (pair_terms); step 2 ends when that is below
+//      PTarget (or when no pair needs a rotation).
 //
 // The rotation of a pair is the symmetric 2x2 Schur decomposition with the
 // smaller angle (Golub & Van Loan, Matrix Computations, Sec. 8.5), written
@@ -316,7 +317,7 @@ __device__ __forceinline__ int eig_core(EigLds<NMAX>& sh, int n, bool warm, doub
         const double sii = sh.sd[i], sjj = sh.sd[j], mii = sh.md[i], mjj = sh.md[j];
         const double di = fma(-mii, sii, sii), dj = fma(-mjj, sjj, sjj);
         // (the Gram overflowed: NaN from here into P, and the solve says so)
-        const double ri = di <= kTiny2 ? 0.0 : rsqrt_pos(di), rj = dj <= kTiny2 ? 0.0 : rsqrt_pos(dj);
+        const double ri = rsqrt_or_zero(di), rj = rsqrt_or_zero(dj);
         const double si = di * ri, sj = dj * rj;
         const double wi = si <= tau ? 0.0 : fma(-tau, ri, 1.0), wj = sj <= tau ? 0.0 : fma(-tau, rj, 1.0);
         if (i == j) {
@@ -327,7 +328,7 @@ __device__ __forceinline__ int eig_core(EigLds<NMAX>& sh, int n, bool warm, doub
         } else {
           const double m = have_c ? B[i * LD + j] : 0.0;
           const double e = fma(-0.5 * m, sii + sjj, G[i * LD + j]);
-          const PairTerms pt = pair_terms<T>(e, di, dj, si, sj, wi, wj, tau, n);
+          const PairTerms pt = pair_terms<T>(e, di, dj, si, sj, ri, rj, wi, wj, tau, n);
           const double z = fma(-0.5 * m, wi + wj, pt.z);
           B[i * LD + j] = z;
           B[j * LD + i] = z;

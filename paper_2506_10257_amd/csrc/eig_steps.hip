@@ -265,7 +265,7 @@ __device__ inline d4 load_block(const double* M, int nb, int bi, int bj) {
 template <typename T, bool TEAM>
 __global__ void __launch_bounds__(kStepThreads)
 k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids, int64_t ticks) {
-  __shared__ double dg[kEigHugeMaxN], sg[kEigHugeMaxN], w[kEigHugeMaxN], sd[kEigHugeMaxN];
+  __shared__ double dg[kEigHugeMaxN], sg[kEigHugeMaxN], rg[kEigHugeMaxN], w[kEigHugeMaxN], sd[kEigHugeMaxN];
   __shared__ double tbuf[kStepWaves][16 * kTrLd];
   __shared__ double scal[kScalars];
   __shared__ unsigned mx[2][4];
@@ -396,11 +396,12 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
     if (tid < n) {
       const double sii = ld<TEAM>(as_global<double>(static_cast<const void*>(e.S + tid * (nb + 1))));
       const double m = ld<TEAM>(as_global<double>(static_cast<const void*>(e.C + tid * (nb + 1)))) - 1.0;
-      const double di = fma(-m, sii, sii), si = sqrt_or_zero(di);
-      const double wi = si <= tau ? 0.0 : 1.0 - tau * rcp_pos(si);
+      const double di = fma(-m, sii, sii), ri = rsqrt_or_zero(di), si = di * ri;
+      const double wi = si <= tau ? 0.0 : fma(-tau, ri, 1.0);
       sd[tid] = sii;
       dg[tid] = di;
       sg[tid] = si;
+      rg[tid] = ri;
       w[tid] = wi;
     }
     __syncthreads();
@@ -420,7 +421,7 @@ k_eig_steps(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids
           mm = fmaxf(mm, cb[r] == cb[r] ? fabsf(static_cast<float>(m)) : INFINITY);
         } else {
           const double el = fma(-0.5 * cb[r], sd[i] + sd[j], sb[r]);
-          const PairTerms pt = pair_terms<T>(el, dg[i], dg[j], sg[i], sg[j], w[i], w[j], tau, n);
+          const PairTerms pt = pair_terms<T>(el, dg[i], dg[j], sg[i], sg[j], rg[i], rg[j], w[i], w[j], tau, n);
           z[r] = fma(-0.5 * cb[r], w[i] + w[j], pt.z);
           k[r] = pt.t;
           mz = fmaxf(mz, pt.mz);

@@ -400,7 +400,7 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
   auto small_rotations = [&] {
     constexpr float kUnit = 1048576.0f;  // 144 tangents of 0.5 fit 32 bits
     if (tid < n) {
-      w[tid] = sqrt_or_zero(Gp[pk(tid, tid)]);
+      w[tid] = rsqrt_or_zero(Gp[pk(tid, tid)]);
       rsum[tid] = 0u;
     }
     __syncthreads();
@@ -408,9 +408,9 @@ k_eig_wide(const SolveDesc* __restrict__ descs, const int32_t* __restrict__ ids,
     for (int idx = tid; idx < n * (n + 1) / 2; idx += NT) {
       const int j = packed_col(idx), i = idx - j * (j + 1) / 2;
       if (i == j) continue;
-      const double si = w[i], sj = w[j];
-      const double wi = si > tau ? 1.0 - tau * rcp_pos(si) : 0.0, wj = sj > tau ? 1.0 - tau * rcp_pos(sj) : 0.0;
-      const PairTerms pt = pair_terms<T>(Gp[idx], Gp[pk(i, i)], Gp[pk(j, j)], si, sj, wi, wj, tau, n);
+      const double di = Gp[pk(i, i)], dj = Gp[pk(j, j)], ri = w[i], rj = w[j], si = di * ri, sj = dj * rj;
+      const double wi = si > tau ? fma(-tau, ri, 1.0) : 0.0, wj = sj > tau ? fma(-tau, rj, 1.0) : 0.0;
+      const PairTerms pt = pair_terms<T>(Gp[idx], di, dj, si, sj, ri, rj, wi, wj, tau, n);
       const float t = fabsf(static_cast<float>(pt.t));
       if (!(t <= static_cast<float>(kTangentMax))) large = 1;  // NaN
       const unsigned u = static_cast<unsigned>(t * kUnit);

@@ -1,0 +1,48 @@
+"""A column whose norm is the threshold itself, to rounding, beside columns that
+are far from orthogonal to it: the eigensolver may not take that diagonal entry
+for a converged one whose weight is (nearly) zero."""
+import numpy as np
+import pytest
+
+import paper_2506_10257_amd as rp
+from oracle import rpca
+
+from .gpu_helpers import device, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(X, dtype, **kw):
+    ref = rpca(X, tol=0.0, **kw)
+    M = to_dev(X, dtype)
+    bar = (1e-10 if dtype == np.float64 else 1e-4) * np.linalg.norm(X)
+    for r in (rp.solve(M, tol=0.0, **kw), rp.solve_many([M, M.clone()], tol=0.0, **kw)[1]):
+        for got, want in ((r.L, ref.L), (r.S, ref.S)):
+            assert np.linalg.norm(to_host(got) - want) <= bar
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [2, 4, 10, 16, 20, 40, 64, 65, 100])
+def test_one_column_at_the_threshold(n, dtype):
+    device()
+    g = np.random.default_rng(n)
+    for _ in range(12):
+        v = np.float32(g.uniform(0.5, 2.0))
+        X = np.full((4, n), 0.5 / np.sqrt(n) * v)  # the others keep below it whatever their own pairs do
+        X[:, 0] = v  # of norm 2 v = 1 / mu
+        _check(X.astype(np.float32).astype(np.float64), dtype, mu=1.0 / (2.0 * float(v)), maxit=2)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_one_row_of_four(dtype):
+    """m = 1, n = 4: lambda = 1/2, so the clipped entry of the second iterate is
+    1 / mu."""
+    device()
+    g = np.random.default_rng(4)
+    Xs = [g.standard_normal((1, 4)).astype(np.float32).astype(np.float64) for _ in range(600)]
+    for k in (2, 6):
+        many = rp.solve_many([to_dev(X, dtype) for X in Xs], tol=0.0, maxit=k)
+        for X, r in zip(Xs, many):
+            ref = rpca(X, tol=0.0, maxit=k)
+            bar = (1e-10 if dtype == np.float64 else 1e-4) * np.linalg.norm(X)
+            assert np.linalg.norm(to_host(r.L) - ref.L) <= bar, X
