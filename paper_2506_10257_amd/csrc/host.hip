@@ -819,9 +819,9 @@ int lease_lanes(int dev, int nlanes, int count, LaneLease& lease, Lanes& view) {
 // Whole-solve kernel (resident_impl.h): chosen for a single solve on the
 // register kernel with one tile per slot whose tiles fit the device's CUs, two
 // per workgroup, or four for FP32 windows of up to 20 frames: more do not fit
-// the registers (the instances with four tiles keep 48 to 136 bytes per lane in
+// the registers (the instances with four tiles keep 48 to 144 bytes per lane in
 // scratch memory as it is; FP64 windows of 21 to 32 frames have not been tried).  Iteration in the kernel / launched (us): 512 x 512 x 20 FP32
-// 36 / 49, 128 x 128 x 20 FP64 25 / 39; 60 of 338 x 260 x 20 FP32 1.6 / 3.0 ms.  With kernel
+// 37 / 49, 128 x 128 x 20 FP64 25 / 39; 60 of 338 x 260 x 20 FP32 1.7 / 3.0 ms.  With kernel
 // timing on, beside other calls (device_use.h) and above kResidentMaxIt iterations, the
 // launches are used.
 constexpr int kResidentMaxIt = 1000;  // one launch holds the device for 45 ms at most

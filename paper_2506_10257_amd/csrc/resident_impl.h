@@ -31,10 +31,10 @@
 // kernel; the others then give up as well, and the caller runs the launched
 // path from the unchanged inputs.
 //
-// Bound by latency: at 512 x 512 x 20 FP32 an iteration takes 36 us (launched,
-// with the same eigensolver, 49): eigensolve 9, update 5.4, Gram 7.4, partial
-// 3.9, first hop and sum 6.3, second hop 2.8; at 128 x 128 x 20 FP64 25 us (39):
-// 12, 2.5, 1.9, 1.5, 4.7, 2.8.
+// Bound by latency: at 512 x 512 x 20 FP32 an iteration takes 37 us (launched,
+// with the same eigensolver, 49): eigensolve 9, update 6.0, Gram 8.2, partial
+// 3.8, first hop and sum 6.4, second hop 2.7; at 128 x 128 x 20 FP64 25 us (39):
+// 11.3, 3.1, 1.9, 1.5, 4.7, 2.6.
 //
 // The arithmetic is that of k_stream, k_reduce_groups and k_eig operation for
 // operation, so the results are bitwise those of the launched path.
